@@ -2,10 +2,12 @@
 C ABI of include/bcjr.h) and libissue_rates.so (the VALU issue-rate probe
 the benchmark prices its roofline with).
 
-libbcjr.so links two translation units: bcjr_capi.hip (the C ABI and every
-kernel family) and bcjr_rot.hip (the rotating-exchange kernel of the
-S = 65536, k = 2 fwd + dW call), which is compiled with the AMDGPU max-ilp
-instruction scheduler; each object carries its own code object."""
+libbcjr.so links three translation units, compiled side by side:
+bcjr_capi.hip (the C ABI and most kernel families), bcjr_rot.hip (the
+rotating-exchange kernels of S = 65536, k = 2), which is compiled with the
+AMDGPU max-ilp instruction scheduler, and bcjr_lin.hip (the linear-domain
+kernels of the smaller trellises); each object carries its own code
+object."""
 from __future__ import annotations
 
 import os
@@ -13,6 +15,7 @@ import shutil
 import subprocess
 import sys
 import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -21,13 +24,15 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libbcjr.so")
 # (source, extra compiler flags)
 UNITS = [(os.path.join(CSRC, "bcjr_capi.hip"), []),
-         (os.path.join(CSRC, "bcjr_rot.hip"), ["-mllvm", "-amdgpu-sched-strategy=max-ilp"])]
+         (os.path.join(CSRC, "bcjr_rot.hip"), ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]),
+         (os.path.join(CSRC, "bcjr_lin.hip"), [])]
 SOURCES = [u[0] for u in UNITS]
 RATES_SRC = os.path.join(CSRC, "issue_rates.hip")
 RATES_LIB = os.path.join(PKG, "libissue_rates.so")
 DEPENDS = SOURCES + [os.path.join(CSRC, f) for f in (
     "bcjr_device.h", "bcjr_kernels.h", "bcjr_vec_kernels.h", "bcjr_qat.h", "bcjr_internal.h",
-    "bcjr_generic_kernels.h", "bcjr_ldlq_kernels.h", "bcjr_rot_kernels.h", "bcjr_pruned_kernels.h")] + [
+    "bcjr_generic_kernels.h", "bcjr_ldlq_kernels.h", "bcjr_rot_kernels.h", "bcjr_pruned_kernels.h",
+    "bcjr_lin_kernels.h")] + [
     os.path.join(INCLUDE, "bcjr.h")]
 
 BASE_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -66,11 +71,12 @@ def _compile_units(units, out, verbose):
     """Each unit to an object with its own flags, then one shared library."""
     tmp = out + ".tmp"
     with tempfile.TemporaryDirectory(prefix="bcjr_build_") as d:
-        objs = []
-        for src, flags in units:
-            obj = os.path.join(d, os.path.splitext(os.path.basename(src))[0] + ".o")
-            _run([hipcc()] + BASE_FLAGS + flags + ["-c", "-I", INCLUDE, "-I", CSRC, "-o", obj, src], verbose)
-            objs.append(obj)
+        objs = [os.path.join(d, os.path.splitext(os.path.basename(src))[0] + ".o") for src, _ in units]
+        with ThreadPoolExecutor(len(units)) as pool:
+            for f in [pool.submit(_run, [hipcc()] + BASE_FLAGS + flags +
+                                  ["-c", "-I", INCLUDE, "-I", CSRC, "-o", obj, src], verbose)
+                      for (src, flags), obj in zip(units, objs)]:
+                f.result()
         _run([hipcc(), "--offload-arch=gfx950", "-fPIC", "-shared", "-o", tmp] + objs, verbose)
     os.replace(tmp, out)
     return out

@@ -34,6 +34,9 @@ int fb_rot_launch(unsigned grid, size_t lds, hipStream_t stream, const FbArgs& a
 const void* fb_lin_kernel(bool vjp);
 int fb_lin_threads();
 int fb_lin_launch(bool vjp, unsigned grid, size_t lds, hipStream_t stream, const FbArgs& a);
+// the linear-domain kernels of the smaller trellises (bcjr_lin.hip)
+LinShape lin_shape(int n, int k, bool vjp, bool dc);
+int lin_launch(const LinShape& s, unsigned grid, hipStream_t stream, LinArgs a);
 
 namespace {
 
@@ -517,7 +520,7 @@ int run_fb_hp(const float* w, int64_t B, int64_t L, const float* codebook, int n
       hipLaunchKernelGGL(dc_reduce_add_kernel, dim3((unsigned)ceil_div(S, 256)), dim3(256), 0, stream,
                          a.dc_part, used, S, dc_add);
     else
-      hipLaunchKernelGGL(dc_reduce_kernel, dim3((unsigned)ceil_div(S, 256)), dim3(256), 0, stream,
+      hipLaunchKernelGGL(dc_reduce_kernel, dim3((unsigned)ceil_div(S, 16)), dim3(256), 0, stream,
                          a.dc_part, used, S, dCodebook);
     if (hipGetLastError() != hipSuccess) return BCJR_ERR_HIP;
   }
@@ -654,6 +657,98 @@ int run_fb_pruned(const float* w, int64_t B, int64_t L, const float* codebook, i
   return BCJR_OK;
 }
 
+int reduce_dc(const double* part, int64_t slots, int64_t S, float* out, hipStream_t stream) {
+  hipLaunchKernelGGL(dc_reduce_kernel, dim3((unsigned)ceil_div(S, 16)), dim3(256), 0, stream, part, slots, S,
+                     out);
+  return hipGetLastError() == hipSuccess ? BCJR_OK : BCJR_ERR_HIP;
+}
+
+// The linear-domain kernels below 65536 states (bcjr_lin_kernels.h): the soft
+// codeword to the field scale of the 65536-state one, the VJP, with or
+// without dCodebook, where fp32 log vectors serve it (T >= 0.04).
+bool lin_small_ok(int n, int k, float T, bool vjp) {
+  if (!supported(n, k) || (n == 16 && k == 2)) return false;
+  return vjp ? !use_high_precision(T) : 1.4426950408889634074 / (2.0 * (double)T) <= kLinearK2;
+}
+
+// [scaled codebook][block flags][dCodebook partials][exponents][histories].
+// The blocks the first launch marks are recomputed by fb_kernel in its repair
+// mode over the history memory, their dCodebook added to the partials.
+// BCJR_ERR_WORKSPACE: too little for it, the caller takes the log-domain path.
+int run_lin_small(const float* w, int64_t B, int64_t L, const float* codebook, int n, int k, float T,
+                  const float* g, float* w_soft, float* logZ, float* dW, float* dCodebook, void* workspace,
+                  size_t ws_bytes, hipStream_t stream, bool vjp) {
+  const bool dc = vjp && dCodebook != nullptr;
+  const LinShape sh = lin_shape(n, k, vjp, dc);
+  const Family f = fb_family(n, k, dc);
+  FbFn rep = fb_pick(n, k, f, vjp, dc);
+  if (!sh.fn || !rep) return BCJR_ERR_WORKSPACE;
+  const int64_t front = (int64_t)(cs_bytes(n) + flag_bytes(B));
+  const int64_t S = (int64_t)1 << n;
+  const int64_t hist = L * (vjp ? 2 : 1) * (S >> k) * (int64_t)sizeof(float);
+  const int64_t dcb = dc ? S * (int64_t)sizeof(double) : 0;
+  const int64_t exb = L * (int64_t)sizeof(int32_t);
+  // the repair pass runs whole workgroups of f.bpw slots over the history
+  // memory, no more slots than there are partials
+  const FbLayout lay = fb_layout(L, n, k, vjp, dc);
+  const int64_t rep_wg = f.bpw * (int64_t)(lay.hist + lay.histGA + lay.small);
+  const int64_t region = (int64_t)ws_bytes - front - (int64_t)kAlign;
+  if (region < rep_wg) return BCJR_ERR_WORKSPACE;
+  const int64_t fit = std::min<int64_t>((region - (int64_t)kAlign) / (hist + exb + dcb),
+                                        dcb ? (region - rep_wg) / dcb : B);
+  Family fl;
+  fl.nt = sh.nt;
+  fl.bpw = sh.bpw;
+  int herr = 0;
+  const int64_t grid = grid_size(sh.fn, fl, sh.lds, B, (size_t)fit, 1, &herr);
+  if (herr) return BCJR_ERR_HIP;
+  const int64_t slots = grid * sh.bpw;
+  if (grid < 1 || slots < std::min<int64_t>(B, f.bpw)) return BCJR_ERR_WORKSPACE;
+  char* p = static_cast<char*>(workspace);
+  float* cs = reinterpret_cast<float*>(p);
+  int32_t* flags = reinterpret_cast<int32_t*>(p + cs_bytes(n));
+  p += front;
+  double* part = dc ? reinterpret_cast<double*>(p) : nullptr;
+  p += align_up((size_t)(slots * dcb));
+  char* base = p;  // shared: the first pass's exponents and histories, then the repair pass's memory
+  int32_t* exps = reinterpret_cast<int32_t*>(base);
+  const int64_t rest = static_cast<char*>(workspace) + ws_bytes - base;
+  const int64_t rgrid = std::min<int64_t>(
+      std::min<int64_t>(ceil_div(B, f.bpw), (int64_t)kDeviceCUs * f.occ_est),
+      std::min<int64_t>(std::max<int64_t>(slots / f.bpw, 1), rest / rep_wg));
+  if (rgrid < 1) return BCJR_ERR_WORKSPACE;
+  const double Td = (double)T, k2 = 1.4426950408889634074 / (2.0 * Td);
+  LinArgs la = {};
+  la.w = w; la.g = g; la.c = codebook; la.cs = cs; la.B = B; la.L = L; la.n = n;
+  la.kap = (float)std::sqrt(k2);
+  la.inv_kap = (float)(1.0 / (double)la.kap);
+  la.dws = (float)(1.0 / ((double)la.kap * (double)la.kap * Td));
+  la.w_soft = w_soft; la.logZ = logZ; la.dW = dW;
+  la.dc_part = part; la.exps = exps; la.flags = flags;
+  la.hist = reinterpret_cast<float*>(base + align_up((size_t)(slots * exb)));
+  if (lin_launch(sh, (unsigned)grid, stream, la) != 0) return BCJR_ERR_HIP;
+  FbArgs a = {};
+  a.w = w; a.g = g; a.c = codebook; a.cs = cs; a.B = B; a.L = L; a.n = n; a.sgt = f.sgt;
+  a.k2 = (float)k2;
+  a.invT = (float)(1.0 / Td);
+  a.kap = la.kap; a.inv_kap = la.inv_kap; a.dws = la.dws;
+  a.w_soft = w_soft; a.logZ = logZ; a.dW = dW;
+  a.flags = flags;
+  a.repair = 1;
+  const int64_t rslots = rgrid * f.bpw;
+  a.histH = vjp ? nullptr : reinterpret_cast<float*>(base);
+  a.histHB = vjp ? reinterpret_cast<float*>(base) : nullptr;
+  a.histGA = dc ? reinterpret_cast<float*>(base + rslots * lay.hist) : nullptr;
+  a.small = reinterpret_cast<float*>(base + rslots * (lay.hist + lay.histGA));
+  a.dc_part = part;
+  const size_t lds = fb_lds_bytes(f, n, k);
+  if (hipFuncSetAttribute((const void*)rep, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    return BCJR_ERR_HIP;
+  hipLaunchKernelGGL(rep, dim3((unsigned)rgrid), dim3(f.nt), lds, stream, a);
+  if (hipGetLastError() != hipSuccess) return BCJR_ERR_HIP;
+  return dc ? reduce_dc(part, slots, S, dCodebook, stream) : BCJR_OK;
+}
+
 // The linear-domain kernel (S = 65536, k = 2, T >= 0.0206; the soft
 // codeword alone, or with dW): [scaled codebook][block flags][slots:
 // lin_layout].  The blocks it marks are recomputed in a repair pass over the
@@ -738,6 +833,11 @@ int run_fb(const float* w, int64_t B, int64_t L, const float* codebook, int n, i
   if (!dCodebook && linear_ok(n, k, T))
     return run_fb_lin(w, B, L, codebook, n, k, T, g, w_soft, logZ, dW, workspace, ws_bytes, stream,
                       vjp);
+  if (lin_small_ok(n, k, T, vjp)) {
+    const int st = run_lin_small(w, B, L, codebook, n, k, T, g, w_soft, logZ, dW, dCodebook, workspace,
+                                 ws_bytes, stream, vjp);
+    if (st != BCJR_ERR_WORKSPACE) return st;  // (a workspace too small for it: the log-domain kernel)
+  }
   if (vjp && pruned_ok(n, k, T, L)) {
     const int st = run_fb_pruned(w, B, L, codebook, n, k, T, g, w_soft, logZ, dW, dCodebook, workspace,
                                  ws_bytes, stream);
@@ -795,7 +895,7 @@ int run_fb(const float* w, int64_t B, int64_t L, const float* codebook, int n, i
   if (hipGetLastError() != hipSuccess) return BCJR_ERR_HIP;
   if (dc) {
     const int64_t used = slots < B ? slots : B;
-    hipLaunchKernelGGL(dc_reduce_kernel, dim3((unsigned)ceil_div(S, 256)), dim3(256), 0, stream,
+    hipLaunchKernelGGL(dc_reduce_kernel, dim3((unsigned)ceil_div(S, 16)), dim3(256), 0, stream,
                        a.dc_part, used, S, dCodebook);
     if (hipGetLastError() != hipSuccess) return BCJR_ERR_HIP;
   }
@@ -1017,7 +1117,7 @@ int run_fbv_hp(const float* w, int64_t B, int64_t L, const float* codebook, int 
   if (hipGetLastError() != hipSuccess) return BCJR_ERR_HIP;
   if (dc) {
     const int64_t used = slots < B ? slots : B;
-    hipLaunchKernelGGL(dc_reduce_kernel, dim3((unsigned)ceil_div(S2, 256)), dim3(256), 0, stream,
+    hipLaunchKernelGGL(dc_reduce_kernel, dim3((unsigned)ceil_div(S2, 16)), dim3(256), 0, stream,
                        a.dc_part, used, S2, dCodebook);
     if (hipGetLastError() != hipSuccess) return BCJR_ERR_HIP;
   }
@@ -1069,7 +1169,7 @@ int run_fbv(const float* w, int64_t B, int64_t L, const float* codebook, int n, 
   if (hipGetLastError() != hipSuccess) return BCJR_ERR_HIP;
   if (dc) {
     const int64_t used = slots < B ? slots : B;
-    hipLaunchKernelGGL(dc_reduce_kernel, dim3((unsigned)ceil_div(S2, 256)), dim3(256), 0, stream,
+    hipLaunchKernelGGL(dc_reduce_kernel, dim3((unsigned)ceil_div(S2, 16)), dim3(256), 0, stream,
                        a.dc_part, used, S2, dCodebook);
     if (hipGetLastError() != hipSuccess) return BCJR_ERR_HIP;
   }

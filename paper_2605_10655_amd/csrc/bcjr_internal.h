@@ -1,6 +1,7 @@
 // bcjr_internal.h -- kernel argument blocks shared by the host dispatcher and
 // the kernels.  Not part of the public ABI.
 #pragma once
+#include <stddef.h>
 #include <stdint.h>
 
 namespace bcjr {
@@ -44,6 +45,33 @@ struct FbArgs {
   // with `repair` set, the log-domain kernel runs only the blocks marked 1
   int32_t* flags;      // [B] or null
   int repair;
+};
+
+// The linear-domain kernels below 65536 states (bcjr_lin_kernels.h).
+struct LinArgs {
+  const float* w;      // [B, L]
+  const float* g;      // [B, L] upstream gradient (VJP only)
+  const float* c;      // [S]
+  float* cs;           // [S] codebook times kappa, written for the second launch
+  int64_t B, L;
+  int n;
+  float kap, inv_kap;  // sqrt(log2(e) / 2T) and its reciprocal
+  float dws;           // 1 / (kappa^2 T)
+  float* w_soft;       // [B, L] or null
+  float* logZ;         // [B] or null
+  float* dW;           // [B, L] or null
+  double* dc_part;     // [slots][S] partial sums of dCodebook
+  float* hist;         // [slots][L][S/K] H, or [slots][L][2][S/K] H, H B (VJP)
+  int32_t* exps;       // [slots][L] exponents of the stored H
+  int32_t* flags;      // [B]
+};
+
+// How a shape runs on them: kernel, threads and blocks per workgroup, LDS
+// bytes; fn is null where they do not serve it.
+struct LinShape {
+  const void* fn = nullptr;
+  int nt = 0, bpw = 0;
+  size_t lds = 0;
 };
 
 // Bytes of one history step of the low-temperature kernel: 9 per group

@@ -126,20 +126,23 @@ __global__ void __launch_bounds__(NT) fb_kernel(FbArgs a) {
     }
   }
 
-  // repair pass of the soft codeword after the linear-domain kernel (one
-  // block per workgroup): only the blocks it marked
-  const bool repair = !VJP && BPW == 1 && a.repair;
+  // repair pass after a linear-domain kernel: only the blocks it marked (the
+  // dCodebook partials then hold that kernel's sums and are added to)
+  const bool repair = a.repair != 0;
   if (repair) {
     int any = 0;
-    for (int64_t base = blockIdx.x; base < a.B; base += gridDim.x) any |= ld_uniform_i(a.flags, base);
-    if (!any) return;
+    for (int64_t b = (int64_t)blockIdx.x * BPW + bw; b < a.B; b += (int64_t)gridDim.x * BPW) any |= a.flags[b];
+    if (!__syncthreads_or(any)) return;
   }
 
   for (int64_t base = (int64_t)blockIdx.x * BPW; base < a.B; base += (int64_t)gridDim.x * BPW) {
-    if (repair && !ld_uniform_i(a.flags, base)) continue;
     const int64_t blk = base + bw;
-    const bool valid = blk < a.B;
+    bool valid = blk < a.B;
     const int64_t bb = valid ? blk : a.B - 1;
+    if (repair) {
+      valid = valid && a.flags[bb] != 0;
+      if (!__syncthreads_or(valid)) continue;
+    }
     const int64_t slot = (int64_t)blockIdx.x * BPW + bw;
     const float* wb = a.w + bb * L;
     const float* gb = VJP ? a.g + bb * L : nullptr;
@@ -171,6 +174,17 @@ __global__ void __launch_bounds__(NT) fb_kernel(FbArgs a) {
     for (int i = tb; i < GS; i += TPB) {
       lds[vb + i] = 0.f;
       if (VJP) lds[vb + GS + i] = 0.f;
+      if (VJP && repair) {  // the rows that the host fills before a first pass
+        const float zero[1] = {0.f};
+        const uint32_t vo = ((uint32_t)bw * (uint32_t)L * hstep + (uint32_t)i) * 4u;
+        const uint32_t so = (uint32_t)(L - 1) * hstep * 4u;
+        buf_st<1, kStream>(hist, vo, so, zero);
+        buf_st<1, kStream>(hist, vo, so + (uint32_t)GS * 4u, zero);
+        if constexpr (DC) {
+          buf_st<1, kStream>(hga, vo, 0, zero);
+          buf_st<1, kStream>(hga, vo, (uint32_t)GS * 4u, zero);
+        }
+      }
     }
     __syncthreads();
     int shiftB = 0;  // sum of the integer shifts of H (exact)
@@ -602,7 +616,7 @@ __global__ void __launch_bounds__(NT) fb_kernel(FbArgs a) {
   // next step's outputs), the (H, B) entries one 16-byte row.
     if constexpr (DC) {
       __syncthreads();  // S1's per-step scalars
-      const bool first = base == (int64_t)blockIdx.x * BPW;
+      const bool first = !repair && base == (int64_t)blockIdx.x * BPW;
       double* part = a.dc_part + slot * ((int64_t)1 << n);
 #pragma unroll 1
       for (int i = 0; i < SGT; ++i) {
@@ -1369,12 +1383,23 @@ __global__ void __launch_bounds__(NT) fb_kernel_hp(FbArgs a) {
   }
 }
 
-__global__ void dc_reduce_kernel(const double* part, int64_t nslots, int64_t S, float* out) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= S) return;
+// 16 states per workgroup, 16 threads over each state's slots: one thread per
+// state left a 4096-state call with 16 workgroups of serial loads (114 us).
+__global__ void __launch_bounds__(256) dc_reduce_kernel(const double* part, int64_t nslots, int64_t S, float* out) {
+  __shared__ double sum[16][17];
+  const int si = threadIdx.x & 15, p = threadIdx.x >> 4;
+  const int64_t s = (int64_t)blockIdx.x * 16 + si;
   double acc = 0.0;
-  for (int64_t q = 0; q < nslots; ++q) acc += part[q * S + s];
-  out[s] = (float)acc;
+  if (s < S) {
+#pragma unroll 8
+    for (int64_t q = p; q < nslots; q += 16) acc += part[q * S + s];
+  }
+  sum[p][si] = acc;
+  __syncthreads();
+  if (p == 0 && s < S) {
+    for (int q = 1; q < 16; ++q) acc += sum[q][si];
+    out[s] = (float)acc;
+  }
 }
 
 // c'(s) = kappa c(s): the codebook in the scaled units of fb_kernel.

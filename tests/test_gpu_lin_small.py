@@ -1,0 +1,108 @@
+"""GPU parity of the linear-domain kernels below 65536 states
+(lin_group_kernel, lin_sg_kernel): every (state bits, k) shape they serve, at
+block lengths around their chunks of steps (one lane chunk is 2 to 64 steps, a
+batch of moments 2 or 4), with block counts that leave a wave's last blocks
+empty, and blocks they mark for the log-domain repair pass (weights outside
+the codebook's range) among ordinary ones.  Everything is compared with the
+fp64 oracle.
+
+Tolerances as everywhere: w_soft |err| <= 2e-5, logZ 1e-4 relative (of 1 where
+logZ is smaller: it crosses zero at short blocks), gradients 1e-4 of max(|ref_i|, rms(ref)) over the call's whole output.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+import paper_2605_10655_amd as P
+from oracle import oracle as O
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+SHAPES = [(n, 1) for n in range(2, 15)] + [(n, 2) for n in range(4, 16)] + [(n, 3) for n in range(6, 15)]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    P.load_library()
+    yield
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+def grad_err(gpu, ref):
+    ref = np.asarray(ref, np.float64)
+    rms = np.sqrt(np.mean(ref * ref))
+    scale = np.maximum(np.abs(ref), rms)
+    return float((np.abs(gpu.cpu().numpy().astype(np.float64) - ref) / np.where(scale > 0, scale, 1.0)).max())
+
+
+def check(w, c, g, n, k, T, dc, tag):
+    """A term of dCodebook is (w - c)(X - E X) / T, where X sums g (c - w): with
+    a weight at distance D outside the codebook, X carries rounding of 2^-22
+    max|g D| (two roundings of each sweep), and the term D / T times that."""
+    ws, lz, dW, dC = P.bcjr_soft_codeword_fwd_vjp(dev(w), dev(c), n, k, T, dev(g), want_dCodebook=dc)
+    soft, lz0 = P.bcjr_soft_codeword(dev(w), dev(c), n, k, T)
+    ows, olz, odW, odC = O.soft_codeword_vjp(w, c, n, k, T, g)
+    e = [float(np.abs(ws.cpu().numpy() - ows).max()), float(np.abs(soft.cpu().numpy() - ows).max()),
+         float((np.abs(lz.cpu().numpy() - olz) / np.maximum(np.abs(olz), 1.0)).max()),
+         float((np.abs(lz0.cpu().numpy() - olz) / np.maximum(np.abs(olz), 1.0)).max()), grad_err(dW, odW)]
+    slack = 0.0
+    if dc:
+        e.append(grad_err(dC, odC))
+        D = np.maximum(0.0, np.maximum(w - c.max(), c.min() - w))
+        slack = float(D.max() / T * 2.0 ** -22 * np.abs(g * D).max() / np.sqrt(np.mean(odC * odC)))
+    print(f"[lin-small] {tag} errors {['%.1e' % x for x in e]}", file=sys.__stderr__, flush=True)
+    assert e[0] <= 2e-5 and e[1] <= 2e-5
+    assert max(e[2:5]) <= 1e-4
+    assert not dc or e[5] <= 1e-4 + slack
+
+
+@pytest.mark.parametrize("n,k", SHAPES)
+def test_shapes_and_lengths_match_oracle(n, k):
+    r = np.random.default_rng(100 * n + k)
+    c = r.standard_normal(1 << n).astype(np.float32)
+    for L, B, T, dc in ((1, 3, 0.1, True), (2, 5, 0.3, True), (7, 37, 0.05, False),
+                        (66, 3, 0.1, True), (129, 5 if n < 12 else 2, 0.05, True)):
+        w = r.standard_normal((B, L)).astype(np.float32)
+        g = r.standard_normal((B, L)).astype(np.float32)
+        check(w, c, g, n, k, T, dc, f"n={n} k={k} L={L} B={B} T={T} dc={dc}")
+
+
+@pytest.mark.parametrize("n,k", [(4, 2), (7, 1), (8, 2), (9, 3), (10, 2), (12, 2), (13, 3), (14, 2), (15, 2)])
+@pytest.mark.parametrize("dc", [False, True])
+def test_marked_blocks_are_recomputed(n, k, dc):
+    """Blocks 1 and 4 hold weights far outside the codebook (distances of over
+    512 log2 units at T = 0.1), which mark them; the others' results and the
+    sum over blocks must not see what the first pass made of them."""
+    r = np.random.default_rng(7 * n + k)
+    c = r.standard_normal(1 << n).astype(np.float32)
+    w = r.standard_normal((6, 40)).astype(np.float32)
+    w[1, 5] = -14.0
+    w[4, 20] = 15.0
+    w[5, [3, 17]] = [6.0, -6.0]
+    g = r.standard_normal((6, 40)).astype(np.float32)
+    check(w, c, g, n, k, 0.1, dc, f"marked n={n} k={k} dc={dc}")
+
+
+def test_non_finite_weights_stay_in_their_block():
+    """A NaN weight marks its block alone: the other blocks of the wave keep
+    the results they have without it."""
+    r = np.random.default_rng(3)
+    n, k = 6, 2
+    c = r.standard_normal(1 << n).astype(np.float32)
+    w = r.standard_normal((9, 33)).astype(np.float32)
+    g = r.standard_normal((9, 33)).astype(np.float32)
+    a = P.bcjr_soft_codeword_fwd_vjp(dev(w), dev(c), n, k, 0.1, dev(g), want_dCodebook=False)
+    w[4, 10] = np.nan
+    b = P.bcjr_soft_codeword_fwd_vjp(dev(w), dev(c), n, k, 0.1, dev(g), want_dCodebook=False)
+    keep = [0, 1, 2, 3, 5, 6, 7, 8]
+    for x, y in zip(a[:3], b[:3]):
+        assert torch.equal(x[keep], y[keep])
+    assert not torch.isfinite(b[0][4]).all()
