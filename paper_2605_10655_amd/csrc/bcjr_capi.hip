@@ -31,9 +31,9 @@ namespace bcjr {
 const void* fb_rot_kernel();
 int fb_rot_launch(unsigned grid, size_t lds, hipStream_t stream, const FbArgs& a);
 // its linear-domain form (blocks it marks are recomputed by the former)
-const void* fb_lin_kernel(bool vjp);
+const void* fb_lin_kernel(bool vjp, bool dc);
 int fb_lin_threads();
-int fb_lin_launch(bool vjp, unsigned grid, size_t lds, hipStream_t stream, const FbArgs& a);
+int fb_lin_launch(bool vjp, bool dc, unsigned grid, size_t lds, hipStream_t stream, FbArgs a);
 // the linear-domain kernels of the smaller trellises (bcjr_lin.hip)
 LinShape lin_shape(int n, int k, bool vjp, bool dc);
 int lin_launch(const LinShape& s, unsigned grid, hipStream_t stream, LinArgs a);
@@ -749,21 +749,23 @@ int run_lin_small(const float* w, int64_t B, int64_t L, const float* codebook, i
   return dc ? reduce_dc(part, slots, S, dCodebook, stream) : BCJR_OK;
 }
 
-// The linear-domain kernel (S = 65536, k = 2, T >= 0.0206; the soft
-// codeword alone, or with dW): [scaled codebook][block flags][slots:
-// lin_layout].  The blocks it marks are recomputed in a repair pass over the
+// The linear-domain kernel (S = 65536, k = 2, T >= 0.0206: the soft codeword
+// alone, or with dW; T >= 0.04: with dCodebook): [scaled codebook][block
+// flags][dCodebook partials][slots: lin_layout].  The blocks it marks are recomputed in a repair pass over the
 // same slot memory once the first pass is complete: by the log-domain
 // kernels (the soft codeword at any T, the VJP at T >= 0.04), or below
 // T = 0.04 by the double-float VJP kernel centred on those blocks' decoded
 // codewords.
 int run_fb_lin(const float* w, int64_t B, int64_t L, const float* codebook, int n, int k, float T,
-               const float* g, float* w_soft, float* logZ, float* dW, void* workspace,
+               const float* g, float* w_soft, float* logZ, float* dW, float* dCodebook, void* workspace,
                size_t ws_bytes, hipStream_t stream, bool vjp) {
+  const bool dc = vjp && dCodebook != nullptr;
   const Family f = fb_family(n, k, false);
   Family fl = f;
   fl.nt = fb_lin_threads();
   const FbLayout lay = lin_layout(L, n, k, vjp);
   const size_t lds = fb_lds_bytes(fl, n, k);
+  const int64_t S = (int64_t)1 << n;
   const size_t front = cs_bytes(n) + flag_bytes(B);
   if (ws_bytes < front) return BCJR_ERR_WORKSPACE;
   const bool hp = vjp && use_high_precision(T);
@@ -772,22 +774,31 @@ int run_fb_lin(const float* w, int64_t B, int64_t L, const float* codebook, int 
   if (hp && ws_bytes - front < hp_prefix_bytes(B, L) + std::max(hp_layout(L, n, k, false).slot,
                                                                  vit_slot_bytes(L, n, k)))
     return BCJR_ERR_WORKSPACE;
+  // with dCodebook the partials of all slots, then memory shared by the first
+  // pass's slots and the repair pass's (fb_layout with its (G, A) histories)
+  const FbLayout rlay = fb_layout(L, n, k, vjp, dc);
+  const size_t rep_slot = rlay.hist + rlay.histGA + rlay.small;
+  size_t fit = (ws_bytes - front) / (lay.slot + rlay.dc);
+  if (dc) {
+    if (ws_bytes - front < rep_slot) return BCJR_ERR_WORKSPACE;
+    fit = std::min(fit, (ws_bytes - front - rep_slot) / rlay.dc);
+  }
   int herr = 0;
-  const int64_t grid = grid_size(fb_lin_kernel(vjp), fl, lds, B, ws_bytes - front, lay.slot, &herr);
+  const int64_t grid = grid_size(fb_lin_kernel(vjp, dc), fl, lds, B, fit, 1, &herr);
   if (herr) return BCJR_ERR_HIP;
   if (grid < 1) return BCJR_ERR_WORKSPACE;
   const size_t lds_rep = fb_lds_bytes(f, n, k);
-  FbFn soft_fn = vjp ? nullptr : fb_pick(n, k, f, false, false);
-  if (!vjp && !soft_fn) return BCJR_ERR_UNSUPPORTED;
-  const void* rep_kern = vjp ? fb_rot_kernel() : (const void*)soft_fn;
+  FbFn rep_fn = vjp && !dc ? nullptr : fb_pick(n, k, f, vjp, dc);
+  if ((!vjp || dc) && !rep_fn) return BCJR_ERR_UNSUPPORTED;
+  const void* rep_kern = vjp && !dc ? fb_rot_kernel() : (const void*)rep_fn;
   if (!hp && hipFuncSetAttribute(rep_kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_rep) !=
                  hipSuccess)
     return BCJR_ERR_HIP;
   const int64_t slots = grid * f.bpw;
-  const int64_t S = (int64_t)1 << n;
   float* cs = static_cast<float*>(workspace);
   int32_t* flags = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + cs_bytes(n));
-  char* base = static_cast<char*>(workspace) + front;
+  double* part = dc ? reinterpret_cast<double*>(static_cast<char*>(workspace) + front) : nullptr;
+  char* base = static_cast<char*>(workspace) + front + (size_t)slots * rlay.dc;
   FbArgs a = {};
   a.w = w; a.g = g; a.c = codebook; a.cs = cs; a.B = B; a.L = L; a.n = n; a.sgt = f.sgt;
   const double Td = (double)T;
@@ -798,21 +809,29 @@ int run_fb_lin(const float* w, int64_t B, int64_t L, const float* codebook, int 
   a.dws = (float)(1.0 / ((double)a.kap * (double)a.kap * Td));
   a.w_soft = w_soft; a.logZ = logZ; a.dW = dW;
   a.flags = flags;
+  a.dc_part = part;
   hipLaunchKernelGGL(scale_kernel, dim3((unsigned)ceil_div(S, 256)), dim3(256), 0, stream, codebook,
                      a.kap, cs, S);
   if (hipGetLastError() != hipSuccess) return BCJR_ERR_HIP;
   a.histH = vjp ? nullptr : reinterpret_cast<float*>(base);
   a.histHB = vjp ? reinterpret_cast<float*>(base) : nullptr;
   a.small = reinterpret_cast<float*>(base + slots * lay.hist);
-  if (fb_lin_launch(vjp, (unsigned)grid, lds, stream, a) != 0) return BCJR_ERR_HIP;
+  if (fb_lin_launch(vjp, dc, (unsigned)grid, lds, stream, a) != 0) return BCJR_ERR_HIP;
   // ---- repair pass over the marked blocks
   if (hp)
     return run_fb_hp(w, B, L, codebook, n, k, T, g, nullptr, w_soft, logZ, dW, nullptr, base,
                      ws_bytes - front, stream, flags);
   a.repair = 1;
-  if (!vjp) {  // the log-domain soft-codeword kernel writes its own history
-    hipLaunchKernelGGL(soft_fn, dim3((unsigned)grid), dim3(f.nt), lds_rep, stream, a);
-    return hipGetLastError() == hipSuccess ? BCJR_OK : BCJR_ERR_HIP;
+  if (!vjp || dc) {  // fb_kernel fills its fixed history rows itself
+    const int64_t rslots = dc ? std::min<int64_t>(slots, (ws_bytes - front - (size_t)slots * rlay.dc) / rep_slot)
+                              : slots;
+    if (dc) {
+      a.histGA = reinterpret_cast<float*>(base + rslots * rlay.hist);
+      a.small = reinterpret_cast<float*>(base + rslots * (rlay.hist + rlay.histGA));
+    }
+    hipLaunchKernelGGL(rep_fn, dim3((unsigned)rslots), dim3(f.nt), lds_rep, stream, a);
+    if (hipGetLastError() != hipSuccess) return BCJR_ERR_HIP;
+    return dc ? reduce_dc(part, slots, S, dCodebook, stream) : BCJR_OK;
   }
   // log domain: its planar step L - 1 (H, B) entries are zero
   const int64_t hstep = 2 * ((int64_t)1 << (n - k));
@@ -830,9 +849,14 @@ int run_fb(const float* w, int64_t B, int64_t L, const float* codebook, int n, i
   if (!supported(n, k))
     return run_gen(w, B, L, codebook, n, k, T, g, w_soft, logZ, dW, dCodebook, workspace, ws_bytes,
                    stream, vjp);
-  if (!dCodebook && linear_ok(n, k, T))
-    return run_fb_lin(w, B, L, codebook, n, k, T, g, w_soft, logZ, dW, workspace, ws_bytes, stream,
-                      vjp);
+  // with dCodebook only where the log-domain fp32 kernel would serve too: below
+  // T = 0.04 single blocks' dCodebook is up to 2e-4 off in fp32 sums
+  if (linear_ok(n, k, T) && (!dCodebook || !use_high_precision(T))) {
+    const int st = run_fb_lin(w, B, L, codebook, n, k, T, g, w_soft, logZ, dW, dCodebook, workspace, ws_bytes,
+                              stream, vjp);
+    // (a workspace too small for the dCodebook form: the log-domain kernel)
+    if (st != BCJR_ERR_WORKSPACE || !dCodebook) return st;
+  }
   if (lin_small_ok(n, k, T, vjp)) {
     const int st = run_lin_small(w, B, L, codebook, n, k, T, g, w_soft, logZ, dW, dCodebook, workspace,
                                  ws_bytes, stream, vjp);

@@ -431,7 +431,7 @@ __device__ __forceinline__ int exp_of(float x) { return (int)((__float_as_uint(x
 // sum_s alpha_t beta_t departing from Z by more than 2e-4 log2 units -- is
 // marked in a.flags and recomputed by a second launch of the log-domain
 // (or, at field scales above 18, the double-float) kernel in repair mode.
-template <int NT, bool VJP>
+template <int NT, bool VJP, bool DC>
 __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
   constexpr int KB = 2, K = 4, n = 16;
   constexpr int GS = 1 << (n - KB);        // 16384 groups
@@ -465,14 +465,36 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
 #pragma unroll
   for (int p = 0; p < TB_BITS; ++p) phtb ^= ((tb0 >> p) & 1u) ? rot::kPhiCol[p] : 0u;
   phtb = rot::rep(phtb);
+  // the codebook rows of the thread's super-groups: resident for the whole
+  // call, or (dCodebook, whose sums take their registers in the forward sweep)
+  // for each backward sweep
   float cbr[SGT][K][K];
+  auto load_cbr = [&]() {
 #pragma unroll
-  for (int i = 0; i < SGT; ++i) {
+    for (int i = 0; i < SGT; ++i) {
 #pragma unroll
-    for (int j = 0; j < K; ++j) buf_ld<K>(cbk, voK, ((j << (n - KB)) + ((i * TPB) << KB)) * 4, cbr[i][j]);
+      for (int j = 0; j < K; ++j) buf_ld<K>(cbk, voK, ((j << (n - KB)) + ((i * TPB) << KB)) * 4, cbr[i][j]);
+    }
+  };
+  if constexpr (!DC) load_cbr();
+  // the slot's dCodebook partial; the lane's offset is rebuilt at each use
+  double* const part = DC ? a.dc_part + (int64_t)blockIdx.x * ((int64_t)1 << n) : nullptr;
+  auto part_at = [&](int i, int j) {
+    const uint32_t o = lane_tid(wave_s) << KB;
+    return part + (o + (uint32_t)((j << (n - KB)) + ((i * TPB) << KB)));
+  };
+  if constexpr (DC) {
+#pragma unroll 1
+    for (int i = 0; i < SGT; ++i)
+      for (int j = 0; j < K; ++j) {
+        double* const pj = part_at(i, j);
+#pragma unroll
+        for (int u = 0; u < K; ++u) pj[u] = 0.0;
+      }
   }
 
   for (int64_t base = blockIdx.x; base < a.B; base += gridDim.x) {
+    if constexpr (DC) load_cbr();
     const int64_t bb = base;
     const int64_t slot = blockIdx.x;
     const int64_t bbu = (int64_t)__builtin_amdgcn_readfirstlane((int)bb);
@@ -498,6 +520,8 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
     int ex = rot::kTopExp;  // exponent of the vector being read
     int off = 0;            // its rescale, folded into this step's exponentials
     float lz2 = 0.f, xbar = 0.f;
+    float rz = 0.f;         // dCodebook: 1 / Z, its exponent apart
+    int exz = 0;
     float wnx = ld_uniform(wbu, L - 1);
     float gnx = VJP ? ld_uniform(gbu, L - 1) : 0.f;
     uint32_t r2 = (uint32_t)(2 * (((L - 1) + 6) % 7));
@@ -505,7 +529,10 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
       const uint32_t tid_s = lane_tid(wave_s);
       const uint32_t vcH = tid_s * 4u;
       rc.red = red0 + ((L - 1 - t) & 1) * (NT / 64) * kRed;
-      const float wt = wnx * kap, gt = gnx;
+      const float wt = wnx * kap;
+      float gt = gnx;
+      // (in a vector register: a multiply with a scalar operand issues at half rate)
+      if constexpr (VJP) pin(gt);
       {
         const int64_t tn = t > 0 ? t - 1 : 0;
         wnx = ld_uniform(wbu, tn);
@@ -552,6 +579,10 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
         if (!(sv[0] > 0.f && sv[0] < INFINITY)) bad = true;
         lz2 = lg2(sv[0]) - (float)(ex - off);
         xbar = sv[1] / sv[0];
+        if constexpr (DC) {
+          rz = 1.f / sv[0];
+          exz = ex - off;
+        }
         if (threadIdx.x == 0 && a.logZ) a.logZ[bb] = (float)((double)lz2 * 0.69314718055994530942);
         __syncthreads();
         break;
@@ -627,6 +658,18 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
     float cprev = 0.f;
     ex = rot::kTopExp;
     off = 0;
+    float acc[DC ? SGT : 1][K][K];   // dCodebook of the block
+    float p0[K][K];                  // codebook rows of the next super-group, one ahead
+    if constexpr (DC) {
+#pragma unroll
+      for (int i = 0; i < SGT; ++i)
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+#pragma unroll
+          for (int u = 0; u < K; ++u) acc[i][j][u] = 0.f;
+#pragma unroll
+      for (int j = 0; j < K; ++j) buf_ld<K>(cbk, lane_tid(wave_s) << (KB + 2), (j << (n - KB)) * 4, p0[j]);
+    }
     float pH[K], pB[K];
     wnx = ld_uniform(wbu, 0);
     gnx = VJP ? ld_uniform(gbu, 0) : 0.f;
@@ -639,7 +682,9 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
       const uint32_t tid_s = lane_tid(wave_s);
       const uint32_t voH_s = tid_s * K * 4u;
       rc.red = red0 + (t & 1) * (NT / 64) * kRed;
-      const float wt = wnx * kap, gt = gnx;
+      const float wt = wnx * kap;
+      float gt = gnx;
+      if constexpr (VJP) pin(gt);
       {
         const int64_t tn = t + 1 < L ? t + 1 : t;
         wnx = ld_uniform(wbu, tn);
@@ -647,6 +692,14 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
       }
       const float eHt = sm_eH[t];
       const float noff = -(float)off;
+      // dCodebook's marginals are alpha H / Z: the step's normalisation in
+      // (g, 1 / (kappa^2 T)), known from the exponents before the step
+      float gsc = 0.f, dsc = 0.f;
+      if constexpr (DC) {
+        const float sc = ldexpf(rz, exz - (ex - off) - (int)eHt);
+        gsc = gt * sc;
+        dsc = dws * sc;
+      }
       const uint32_t rs = __builtin_amdgcn_readfirstlane(r2);
       const uint32_t tslot = rot::slot8(phtb, rs);
       // max G_{t+1}, sum P d, sum P, sum P (X - xbar), sum P (X - xbar) d with
@@ -680,6 +733,17 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
           Hc[u] = pH[u];
           Bc[u] = VJP ? pB[u] : 0.f;
         }
+        float cc[K][K];
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+#pragma unroll
+          for (int u = 0; u < K; ++u) cc[j][u] = DC ? p0[j][u] : cbr[i][j][u];
+        if constexpr (DC) {  // the next super-group's (the first of the next step after the last)
+          const int inx = i + 1 < SGT ? i + 1 : 0;
+#pragma unroll
+          for (int j = 0; j < K; ++j)
+            buf_ld<K>(cbk, voH_s, ((j << (n - KB)) + ((inx * TPB) << KB)) * 4, p0[j]);
+        }
         {
           const bool last = i + 1 >= SGT;
           const int64_t tn = last && t + 1 < L ? t + 1 : t;
@@ -694,7 +758,7 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
             float al[K], q[K], dd[K];
   #pragma unroll
             for (int j = 0; j < K; ++j) {
-              dd[j] = wtl - cbr[i][j][u];
+              dd[j] = wtl - cc[j][u];
               const float e = ex2(fmaf(-dd[j], dd[j], noff));
               al[j] = e * Gin[j];
               q[j] = e * fmaf(-gG[j], dd[j], Ain[j]);
@@ -714,13 +778,22 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
             rv[2] = fmaf(Hu, go, rv[2]);
             rv[3] = fmaf(go, bx, fmaf(Hu, aout, rv[3]));
             rv[4] = fmaf(sad, bx, fmaf(Hu, sqd, rv[4]));
+            if constexpr (DC) {
+              // p (g + d (X - E X) / (kappa^2 T)) of the group's K states
+              const float aq = Hu * gsc, bq = bx * dsc, cq = Hu * dsc;
+#pragma unroll
+              for (int j = 0; j < K; ++j) {
+                acc[i][j][u] = fmaf(dd[j], fmaf(al[j], bq, q[j] * cq), fmaf(al[j], aq, acc[i][j][u]));
+                pin(acc[i][j][u]);  // (or it sinks below the barrier, its inputs live across)
+              }
+            }
             rot::st_pair_at(sl[u], go, aout);
           } else {
             // soft codeword alone: sum alpha, sum alpha d and the two moments
             float al[K], dd[K];
 #pragma unroll
             for (int j = 0; j < K; ++j) {
-              dd[j] = wtl - cbr[i][j][u];
+              dd[j] = wtl - cc[j][u];
               al[j] = ex2(fmaf(-dd[j], dd[j], noff)) * Gin[j];
             }
             const float go = (al[0] + al[1]) + (al[2] + al[3]);
@@ -760,6 +833,19 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
       r2 = r2 == 12u ? 0u : r2 + 2u;
     }
     if (threadIdx.x == 0) a.flags[bb] = bad ? 1 : 0;
+    if constexpr (DC) {
+      if (!bad) {
+#pragma unroll
+        for (int i = 0; i < SGT; ++i)
+#pragma unroll
+          for (int j = 0; j < K; ++j) {
+            double* const pj = part_at(i, j);
+#pragma unroll
+            for (int u = 0; u < K; ++u) pj[u] += (double)acc[i][j][u];
+            asm volatile("" ::: "memory");
+          }
+      }
+    }
     __syncthreads();
   }
 }
