@@ -279,6 +279,9 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
   const int64_t slot = (int64_t)blockIdx.x * bpw + (lane >> (n - KB));
   const int L = (int)a.L;                    // (L x S / K x 12 bytes is below 2^31)
   const float kap = a.kap;
+  // d' = kappa (w - c) as fma(-kappa, c, kappa w): one rounding, relative to d'
+  float nkap = -kap;
+  pin(nkap);
   float dws = a.dws;
   if constexpr (DC) pin(dws);                // (a vector register, see to_vgpr)
   const int rowi = seg0 + ((v << KB) & (GS - 1));   // H(v K + b): K consecutive groups
@@ -289,11 +292,12 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
   float clo = INFINITY, chi = -INFINITY;
 #pragma unroll
   for (int b = 0; b < K; ++b) {
-    cb[b] = a.c[v * K + b] * kap;
-    cf[b] = a.c[b * GS + v] * kap;
-    clo = fminf(clo, cf[b]);
-    chi = fmaxf(chi, cf[b]);
-    if (slot == 0) a.cs[b * GS + v] = cf[b];
+    cb[b] = a.c[v * K + b];
+    cf[b] = a.c[b * GS + v];
+    const float cs = cf[b] * kap;
+    clo = fminf(clo, cs);
+    chi = fmaxf(chi, cs);
+    if (slot == 0) a.cs[b * GS + v] = cs;
   }
   clo = -seg_reduce<true>(-clo, GS);
   chi = seg_reduce<true>(chi, GS);
@@ -355,7 +359,7 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
       float hv = 0.f, bv = 0.f;
 #pragma unroll
       for (int b = 0; b < K; ++b) {
-        const float d = wt - cb[b];
+        const float d = fmaf(nkap, cb[b], wt);
         const float e = ex2(fmaf(-d, d, noff));
         hv = fmaf(e, in[b].x, hv);
         if constexpr (VJP) bv = fmaf(e, fmaf(-gt * in[b].x, d, in[b].y), bv);
@@ -389,7 +393,7 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
       float ls = 0.f, ly = 0.f;
 #pragma unroll
       for (int j = 0; j < K; ++j) {
-        const float d = wt - cf[j];
+        const float d = fmaf(nkap, cf[j], wt);
         const float e = ex2(fmaf(-d, d, noff));
         ls = fmaf(e, in.x, ls);
         if constexpr (VJP) ly = fmaf(e, fmaf(-gt * in.x, d, in.y), ly);
@@ -452,7 +456,7 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
 #pragma unroll
           for (int j = 0; j < K; ++j) {
             const float2 in = xw[coli + j * NSG];
-            dd[j] = wt - cf[j];
+            dd[j] = fmaf(nkap, cf[j], wt);
             const float e = ex2(fmaf(-dd[j], dd[j], noff));
             al[j] = e * in.x;
             if constexpr (VJP) qq[j] = e * fmaf(-gt * in.x, dd[j], in.y);
@@ -568,6 +572,9 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
   const int64_t slot = unit * bpw + sub;
   const int L = (int)a.L;                    // (L x S / K x 12 bytes is below 2^31)
   const float kap = a.kap;
+  // d' = kappa (w - c) as fma(-kappa, c, kappa w): one rounding, relative to d'
+  float nkap = -kap;
+  pin(nkap);
   float dws = a.dws;
   if constexpr (DC) pin(dws);                // (a vector register, see to_vgpr)
 
@@ -612,13 +619,14 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
     for (int j = 0; j < K; ++j) {
       const uint32_t so = ((j << (n - KB)) + ((i * TPB) << KB)) * 4;
       buf_ld<K>(cbk, voK, so, cc[i][j]);
+      float cs[K];
 #pragma unroll
       for (int u = 0; u < K; ++u) {
-        cc[i][j][u] *= kap;
-        clo = fminf(clo, cc[i][j][u]);
-        chi = fmaxf(chi, cc[i][j][u]);
+        cs[u] = cc[i][j][u] * kap;
+        clo = fminf(clo, cs[u]);
+        chi = fmaxf(chi, cs[u]);
       }
-      if (slot == 0) st_vec<K>(a.cs + (voK + so) / 4, cc[i][j]);
+      if (slot == 0) st_vec<K>(a.cs + (voK + so) / 4, cs);
     }
   }
   {  // the codebook's range over the block
@@ -721,7 +729,7 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
           float e[K], d[K];
 #pragma unroll
           for (int b = 0; b < K; ++b) {
-            d[b] = wtl - cc[i][j][b];
+            d[b] = fmaf(nkap, cc[i][j][b], wtl);
             e[b] = ex2(fmaf(-d[b], d[b], noff));
           }
           float hv[1] = {e[0] * Hin[0]};
@@ -772,7 +780,7 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
         for (int j = 0; j < K; ++j) {
 #pragma unroll
           for (int b = 0; b < K; ++b) {
-            const float d = wt - cc[i][j][b];
+            const float d = fmaf(nkap, cc[i][j][b], wt);
             const float e = ex2(fmaf(-d, d, noff));
             sv[0] = fmaf(e, Hin[b], sv[0]);
             if constexpr (VJP) sv[1] = fmaf(e, fmaf(-gt * d, Hin[b], Bin[b]), sv[1]);
@@ -866,7 +874,7 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
           float al[K], qq[K], dd[K];
 #pragma unroll
           for (int j = 0; j < K; ++j) {
-            dd[j] = wtl - cc[i][j][u];
+            dd[j] = fmaf(nkap, cc[i][j][u], wtl);
             const float e = ex2(fmaf(-dd[j], dd[j], noff));
             al[j] = e * Gin[j];
             if constexpr (VJP) qq[j] = e * fmaf(-gG[j], dd[j], Ain[j]);

@@ -402,8 +402,9 @@ __device__ __forceinline__ void st_pair_at(uint32_t addr, float a, float b) {
   *reinterpret_cast<lds_f2*>(addr) = v;
 }
 
-constexpr int kTopExp = 40;                  // a rescale puts the largest entry at 2^40
-constexpr float kTop = 1099511627776.0f;     // 2^40
+constexpr int kTopExp = 50;                  // a rescale puts the largest entry at 2^50
+constexpr float kTop = 0x1p50f;
+constexpr float kFarMax = 512.f;             // log2 units of a weight's distance outside the codebook
 
 // e with x = m 2^e, 1 <= m < 2, for a positive normal x (-127 for zero or a
 // denormal, 128 for inf or NaN)
@@ -418,15 +419,15 @@ __device__ __forceinline__ int exp_of(float x) { return (int)((__float_as_uint(x
 // local field, Eq. boltzmann), and the tangents carried unnormalised
 // (G A and H B), so that a step needs one exponential per state and no
 // logarithm, maximum or reciprocal per group.  After each step the vector
-// is rescaled by an exact power of two that puts its largest entry at 2^40
+// is rescaled by an exact power of two that puts its largest entry at 2^50
 // (the exponent is folded into the next step's exponentials); fp32 then
-// holds every state within ~166 log2 units of the step's maximum at full
+// holds every state within ~176 log2 units of the step's maximum at full
 // precision, where the states that carry the posterior lie within ~60-90
 // at T >= 0.04 on unit-variance data.  The marginals and the four dW moments
 // are products of the two sweeps' values, scale-invariant per step.
 //
 // A block whose vectors leave that range -- a step whose largest entry
-// falls below 2^-30 (a single-step decay of 70 log2 units, which the
+// falls below 2^-30 (a single-step decay of 80 log2 units, which the
 // posterior states would not survive) or the forward's per-step mass
 // sum_s alpha_t beta_t departing from Z by more than 2e-4 log2 units -- is
 // marked in a.flags and recomputed by a second launch of the log-domain
@@ -442,6 +443,13 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
   extern __shared__ float lds[];           // [GS] (value, tangent) pairs, then the reduction area
   const int64_t L = a.L;
   const float kap = a.kap;
+  // d' = kappa w - kappa c.  With dCodebook as fma(-kappa, c, kappa w): it rounds
+  // kappa c with d' alone and leaves the rounding of kappa w, the same for
+  // every state (dCodebook at T = 0.05 1.39e-6 -> 1.17e-6 off the 64-bit
+  // result, on one block 2.3e-6 -> 0.8e-6, for 0.5 % of the call's time)
+  float nkap = -kap;
+  if constexpr (DC) pin(nkap);
+  auto diff = [&](float c, float w) { return DC ? fmaf(nkap, c, w) : w - c; };
 
   RedCtx rc;
   rc.width = 64;
@@ -455,7 +463,7 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
   // block is marked for the repair pass (whose kernels address LDS plainly).
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
   const bool lds_aligned = (lds0 & 0x1FFFFu) == 0u;
-  const rsrc_t cbk = make_rsrc(a.cs, (uint32_t)4 << n);
+  const rsrc_t cbk = make_rsrc(DC ? a.c : a.cs, (uint32_t)4 << n);
   const uint32_t tb0 = threadIdx.x;
   const uint32_t voK = tb0 << (KB + 2);
   // floats per history step: H then (VJP) H B, [S/K] each
@@ -493,6 +501,34 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
       }
   }
 
+  // the codebook's range in scaled units: a step's exponents leave out the
+  // squared distance of a weight outside it (logZ gets the sum back)
+  float clo, chi;
+  {
+    if constexpr (DC) load_cbr();
+    float mm[2] = {-INFINITY, -INFINITY};
+#pragma unroll
+    for (int i = 0; i < SGT; ++i)
+#pragma unroll
+      for (int j = 0; j < K; ++j)
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+          mm[0] = fmaxf(mm[0], -cbr[i][j][u]);
+          mm[1] = fmaxf(mm[1], cbr[i][j][u]);
+        }
+    rc.red = red0;
+    red_pre<2, 3u>(mm, rc);
+    __syncthreads();
+    red_post<2, 3u>(mm, rc);
+    clo = read_lane(-mm[0] * (DC ? kap : 1.f), 0);
+    chi = read_lane(mm[1] * (DC ? kap : 1.f), 0);
+    __syncthreads();
+  }
+  auto far2 = [&](float w) {
+    const float d = fmaxf(0.f, fmaxf(w - chi, clo - w));
+    return d * d;
+  };
+
   for (int64_t base = blockIdx.x; base < a.B; base += gridDim.x) {
     if constexpr (DC) load_cbr();
     const int64_t bb = base;
@@ -514,12 +550,13 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
 
     // ------------------------------------------------------------------ S0
     // Backward: H and the unnormalised tangent H B in the pair slots, in
-    // place; H_{L-1} = 1 is stored as 2^40.
+    // place; H_{L-1} = 1 is stored as 2^50.
     for (int i = threadIdx.x; i < 2 * GS; i += NT) lds[i] = (i & 1) ? 0.f : rot::kTop;
     __syncthreads();
     int ex = rot::kTopExp;  // exponent of the vector being read
     int off = 0;            // its rescale, folded into this step's exponentials
     float lz2 = 0.f, xbar = 0.f;
+    float far = 0.f;        // what the exponents leave out
     float rz = 0.f;         // dCodebook: 1 / Z, its exponent apart
     int exz = 0;
     float wnx = ld_uniform(wbu, L - 1);
@@ -538,7 +575,10 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
         wnx = ld_uniform(wbu, tn);
         if constexpr (VJP) gnx = ld_uniform(gbu, tn);
       }
-      const float noff = -(float)off;
+      const float f2 = far2(wt);
+      if (!(f2 <= rot::kFarMax)) bad = true;
+      far += f2;
+      const float noff = f2 - (float)off;
       const uint32_t rs = __builtin_amdgcn_readfirstlane(r2);
       const uint32_t tslot = rot::slot8(phtb, rs);
       const uint32_t soH = (uint32_t)t * hstep * 4u;
@@ -563,7 +603,7 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
           for (int j = 0; j < K; ++j) {
 #pragma unroll
             for (int b = 0; b < K; ++b) {
-              const float d = wtl - cbr[i][j][b];
+              const float d = diff(cbr[i][j][b], wtl);
               const float e = ex2(fmaf(-d, d, noff));
               ls = fmaf(e, Hin[b], ls);
               if constexpr (VJP) ly = fmaf(e, fmaf(-gt * d, Hin[b], Bin[b]), ly);
@@ -583,7 +623,7 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
           rz = 1.f / sv[0];
           exz = ex - off;
         }
-        if (threadIdx.x == 0 && a.logZ) a.logZ[bb] = (float)((double)lz2 * 0.69314718055994530942);
+        if (threadIdx.x == 0 && a.logZ) a.logZ[bb] = (float)(((double)lz2 - (double)far) * 0.69314718055994530942);
         __syncthreads();
         break;
       }
@@ -611,7 +651,7 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
           float e[K], d[K];
 #pragma unroll
           for (int b = 0; b < K; ++b) {
-            d[b] = wtl - cbr[i][j][b];
+            d[b] = diff(cbr[i][j][b], wtl);
             e[b] = ex2(fmaf(-d[b], d[b], noff));
           }
           float hv0 = e[0] * Hin[0];
@@ -650,7 +690,7 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
 
     // ------------------------------------------------------------------ S1
     // Forward: G and the unnormalised tangent G A in the pair slots, in
-    // place; G_0 = 1 stored as 2^40.  A is centred on g_{t-1} w_soft_{t-1}
+    // place; G_0 = 1 stored as 2^50.  A is centred on g_{t-1} w_soft_{t-1}
     // when it is read (G A - c G).
     for (int i = threadIdx.x; i < 2 * GS; i += NT) lds[i] = (i & 1) ? 0.f : rot::kTop;
     __syncthreads();
@@ -691,7 +731,7 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
         if constexpr (VJP) gnx = ld_uniform(gbu, tn);
       }
       const float eHt = sm_eH[t];
-      const float noff = -(float)off;
+      const float noff = far2(wt) - (float)off;
       // dCodebook's marginals are alpha H / Z: the step's normalisation in
       // (g, 1 / (kappa^2 T)), known from the exponents before the step
       float gsc = 0.f, dsc = 0.f;
@@ -758,7 +798,7 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
             float al[K], q[K], dd[K];
   #pragma unroll
             for (int j = 0; j < K; ++j) {
-              dd[j] = wtl - cc[j][u];
+              dd[j] = diff(cc[j][u], wtl);
               const float e = ex2(fmaf(-dd[j], dd[j], noff));
               al[j] = e * Gin[j];
               q[j] = e * fmaf(-gG[j], dd[j], Ain[j]);
@@ -793,7 +833,7 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
             float al[K], dd[K];
 #pragma unroll
             for (int j = 0; j < K; ++j) {
-              dd[j] = wtl - cc[j][u];
+              dd[j] = diff(cc[j][u], wtl);
               al[j] = ex2(fmaf(-dd[j], dd[j], noff)) * Gin[j];
             }
             const float go = (al[0] + al[1]) + (al[2] + al[3]);
