@@ -809,6 +809,7 @@ int run_fb_lin(const float* w, int64_t B, int64_t L, const float* codebook, int 
   a.dws = (float)(1.0 / ((double)a.kap * (double)a.kap * Td));
   a.w_soft = w_soft; a.logZ = logZ; a.dW = dW;
   a.flags = flags;
+  a.far_max = dc ? 4096.f : hp ? 24.f : 64.f;
   a.dc_part = part;
   hipLaunchKernelGGL(scale_kernel, dim3((unsigned)ceil_div(S, 256)), dim3(256), 0, stream, codebook,
                      a.kap, cs, S);

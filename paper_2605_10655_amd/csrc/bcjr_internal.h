@@ -45,6 +45,8 @@ struct FbArgs {
   // with `repair` set, the log-domain kernel runs only the blocks marked 1
   int32_t* flags;      // [B] or null
   int repair;
+  float far_max;       // linear-domain kernel: log2 units of a weight's distance
+                       // outside the codebook's range that it takes on
 };
 
 // The linear-domain kernels below 65536 states (bcjr_lin_kernels.h).

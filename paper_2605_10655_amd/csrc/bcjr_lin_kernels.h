@@ -94,23 +94,32 @@ constexpr size_t sg_lds(int n, int KB, int SGT, bool VJP) {
          (waves > 1 ? (size_t)waves * (2 * batch(n, KB, SGT) * 16 + 2 * 4) : 0);
 }
 
-constexpr int kTopExp = 60;             // a rescale puts the largest entry at 2^60
-constexpr float kTop = 0x1p60f;
-constexpr uint32_t kFloorBits = 0x30800000u;  // 2^-30: a step's largest entry below this marks the block
-constexpr uint32_t kCeilBits = 0x71800000u;   // 2^100
-constexpr float kFarMax = 512.f;        // log2 units of a weight's distance outside the codebook
+// A rescale puts the largest entry at 2^90.  A step may lower it to 2^-36 (a
+// weight that few states emit, after states far from them): 90 log2 units
+// below it then still hold, and below that the block is marked.  H takes the
+// exponents of both vectors and Z in one ldexp before it meets alpha.
+constexpr int kTopExp = 90;
+constexpr float kTop = 0x1p90f;
+constexpr uint32_t kFloorBits = 0x2D800000u;  // 2^-36
+constexpr uint32_t kCeilBits = 0x79800000u;   // 2^116
+// alpha H of the step's states in the stored units is 2^-es / Z's mantissa: with
+// es above this they lie 200 log2 units below the vectors' largest entries,
+// and H times the scale could leave the range elsewhere
+constexpr int kScaleMax = 20;
+// log2 units of a weight's distance outside the codebook (its exponents round
+// at 6e-8 of them); beyond, the block is marked
+constexpr float kFarMax = 4096.f;
 constexpr float kMassTol = 1.4e-4f;     // departure of the forward mass from Z
 
-// distance of a weight outside [lo, hi], squared: the least -log2 e of a step
-__device__ __forceinline__ float far2(float w, float lo, float hi) {
-  const float d = fmaxf(0.f, fmaxf(w - hi, lo - w));
-  return d * d;
-}
+// how far a weight lies above (below, negative) the range [lo, hi]
+__device__ __forceinline__ float beyond(float w, float lo, float hi) { return w - fminf(fmaxf(w, lo), hi); }
 
 // Holds a step's uniform values in vector registers: on gfx950 v_fma_f32,
 // v_mul_f32 and v_add_f32 with vector operands only issue every 2.4 clocks per
 // SIMD, with one scalar operand every 4.2 (2 and more waves per SIMD).
-__device__ __forceinline__ void to_vgpr(float& a, float& b) { asm volatile("" : "+v"(a), "+v"(b)); }
+__device__ __forceinline__ void to_vgpr(float& a, float& b, float& c) {
+  asm volatile("" : "+v"(a), "+v"(b), "+v"(c));
+}
 
 // 1 / x to one rounding
 __device__ __forceinline__ float inv(float x) {
@@ -151,8 +160,10 @@ __device__ __forceinline__ int rescale(uint32_t bits, bool& bad) {
 }
 
 // The rows of a block, W = 64 or the lanes of its segment: lane l holds entry
-// base + l of w' and g, the distance outside the codebook's range, and (in
-// the forward sweep) the exponents of the stored H.
+// base + l of w' and g, and for a weight outside the codebook's range how far
+// (m) and the whole log2 units (f) that the step's exponents leave out.  Such
+// a step's tangent terms and moments are taken about the edge of the range,
+// not the weight: d - m stays of the size of the codewords' own differences.
 template <int W, bool VJP>
 struct Rows {
   static constexpr int kChunk = W;
@@ -161,7 +172,7 @@ struct Rows {
   int L;
   float kap, lo, hi;
   int li, seg0;          // lane in the segment, its first lane
-  float cw, cg, cf, nw, ng;
+  float cw, cg, cf, cm, nw, ng;
   int base;
 
   __device__ __forceinline__ void load(int b, float& x, float& y) const {
@@ -175,7 +186,8 @@ struct Rows {
     base = b;
     cw = nw * kap;
     if constexpr (VJP) cg = ng;
-    cf = b + li < L ? far2(cw, lo, hi) : 0.f;
+    cm = b + li < L ? beyond(cw, lo, hi) : 0.f;
+    cf = floorf(cm * cm);  // (whole, so that both sweeps take out the same)
     if (!(cf <= kFarMax)) bad = true;
     load(next, nw, ng);
   }
@@ -232,7 +244,8 @@ __device__ __forceinline__ void sum_batch(const float* m, int lane, float (&r)[N
 }
 
 // w_soft_t and dW_t from a step's moments sum P d, sum P, sum P (X - E X),
-// sum P (X - E X) d (P normalised by Z: sum P is the forward mass); wt = w'_t
+// sum P (X - E X) d (P normalised by Z: sum P is the forward mass); wt = w'_t, or the
+// edge of the range that the moments are about
 template <bool VJP>
 __device__ __forceinline__ void step_outputs(const LinArgs& a, int64_t at, float wt, const float* r, bool& bad) {
   const float mass = r[1];
@@ -351,7 +364,8 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
       rw.put_i(ev, ex, t);
       float wt = rw.at(rw.cw, t);
       float gt = VJP ? rw.at(rw.cg, t) : 0.f;
-      lin::to_vgpr(wt, gt);
+      float mf = rw.at(rw.cm, t);
+      lin::to_vgpr(wt, gt, mf);
       const float noff = rw.at(rw.cf, t) - (float)off;
       float2 in[K];
 #pragma unroll
@@ -362,7 +376,7 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
         const float d = fmaf(nkap, cb[b], wt);
         const float e = ex2(fmaf(-d, d, noff));
         hv = fmaf(e, in[b].x, hv);
-        if constexpr (VJP) bv = fmaf(e, fmaf(-gt * in[b].x, d, in[b].y), bv);
+        if constexpr (VJP) bv = fmaf(e, fmaf(-gt * in[b].x, d - mf, in[b].y), bv);
       }
       lin::wave_sync();
       xw[lane] = make_float2(hv, bv);
@@ -387,7 +401,7 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
     float xbar = 0.f, rz;
     int exz;
     {
-      const float wt = rw.at(rw.cw, 0), gt = VJP ? rw.at(rw.cg, 0) : 0.f;
+      const float wt = rw.at(rw.cw, 0), gt = VJP ? rw.at(rw.cg, 0) : 0.f, mf = rw.at(rw.cm, 0);
       const float noff = rw.at(rw.cf, 0) - (float)off;
       const float2 in = xw[lane];
       float ls = 0.f, ly = 0.f;
@@ -396,7 +410,7 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
         const float d = fmaf(nkap, cf[j], wt);
         const float e = ex2(fmaf(-d, d, noff));
         ls = fmaf(e, in.x, ls);
-        if constexpr (VJP) ly = fmaf(e, fmaf(-gt * in.x, d, in.y), ly);
+        if constexpr (VJP) ly = fmaf(e, fmaf(-gt * in.x, d - mf, in.y), ly);
       }
       ls = seg_reduce<false>(ls, GS);
       if constexpr (VJP) ly = seg_reduce<false>(ly, GS);
@@ -442,22 +456,25 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
           }
           float wt = rw.at(rw.cw, t);
           float gt = VJP ? rw.at(rw.cg, t) : 0.f;
-          lin::to_vgpr(wt, gt);
+          float mf = rw.at(rw.cm, t);
+      lin::to_vgpr(wt, gt, mf);
           const float noff = rw.at(rw.cf, t) - (float)off;
           // alpha_t beta_t / Z = alpha H sc, exponents of both vectors and Z;
           // (ex - off: of alpha_t; the stored H_t carries no rescale of its own)
-          const float sc = ldexpf(rz, exz - (ex - off) - rw.at_i(ec, t));
+          const int es = exz - (ex - off) - rw.at_i(ec, t);
+          if (es > lin::kScaleMax) bad = true;
           const float H = ph[q].x, HB = ph[q].y;
           {
             const int tn = t + Q < L ? t + Q : L - 1;
             ph[q] = VJP ? hist2[tn * GS] : make_float2(hist1[tn * GS], 0.f);
           }
-          float al[K], qq[K], dd[K];
+          float al[K], qq[K], dd[K], dw[K];  // d about the edge of the range, and about the weight
 #pragma unroll
           for (int j = 0; j < K; ++j) {
             const float2 in = xw[coli + j * NSG];
-            dd[j] = fmaf(nkap, cf[j], wt);
-            const float e = ex2(fmaf(-dd[j], dd[j], noff));
+            dw[j] = fmaf(nkap, cf[j], wt);
+            dd[j] = dw[j] - mf;
+            const float e = ex2(fmaf(-dw[j], dw[j], noff));
             al[j] = e * in.x;
             if constexpr (VJP) qq[j] = e * fmaf(-gt * in.x, dd[j], in.y);
           }
@@ -477,12 +494,12 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
           }
           lin::wave_sync();
           xw[lane] = make_float2(go, ao);
-          const float Hs = H * sc;
+          const float Hs = ldexpf(H, es) * rz;
           float m[NM];
           m[0] = Hs * sad;
           m[1] = Hs * go;
           if constexpr (VJP) {
-            const float bx = fmaf(-xbar, Hs, HB * sc);
+            const float bx = fmaf(-xbar, Hs, ldexpf(HB, es) * rz);
             m[VJP ? 2 : 0] = fmaf(go, bx, Hs * ao);
             m[VJP ? 3 : 0] = fmaf(sad, bx, Hs * sqd);
             if constexpr (DC) {
@@ -490,7 +507,7 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
               const float aq = Hs * gt, bq = bx * dws, cq = Hs * dws;
 #pragma unroll
               for (int j = 0; j < K; ++j) {
-                acc[j] = fmaf(dd[j], fmaf(al[j], bq, qq[j] * cq), fmaf(al[j], aq, acc[j]));
+                acc[j] = fmaf(dw[j], fmaf(al[j], bq, qq[j] * cq), fmaf(al[j], aq, acc[j]));
                 pin(acc[j]);  // (or it sinks out of the step, its inputs live across)
               }
             }
@@ -509,7 +526,7 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
           } else {
 #pragma unroll
             for (int c = 0; c < NM; ++c) m[c] = seg_reduce<false>(m[c], GS);
-            if (v == 0 && valid) lin::step_outputs<VJP>(a, bb * L + t, wt, m, bad);
+            if (v == 0 && valid) lin::step_outputs<VJP>(a, bb * L + t, wt - mf, m, bad);
           }
           lin::wave_sync();
         }
@@ -520,7 +537,7 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
         float r[NM];
         lin::sum_batch<GS, Q, NM>(mom, ln, r);
         const int t = t0 + (lv / (GS / Q));
-        const float wt = __shfl(rw.cw, (ln & ~(GS - 1)) + t - rw.base);
+        const float wt = __shfl(rw.cw - rw.cm, (ln & ~(GS - 1)) + t - rw.base);
         if (t < L && valid && lv % (GS / Q) == 0) lin::step_outputs<VJP>(a, bb * L + t, wt, r, bad);
         lin::wave_sync();
       }
@@ -709,7 +726,8 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
       rw.put_i(ev, ex, t);
       float wt = rw.at(rw.cw, t);
       float gt = VJP ? rw.at(rw.cg, t) : 0.f;
-      lin::to_vgpr(wt, gt);
+      float mf = rw.at(rw.cm, t);
+      lin::to_vgpr(wt, gt, mf);
       const float noff = rw.at(rw.cf, t) - (float)off;
       const float* const rd = vb + par * PL * GS;
       float* const wr = vb + (par ^ 1) * PL * GS;
@@ -731,6 +749,7 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
           for (int b = 0; b < K; ++b) {
             d[b] = fmaf(nkap, cc[i][j][b], wtl);
             e[b] = ex2(fmaf(-d[b], d[b], noff));
+            if constexpr (VJP) d[b] -= mf;
           }
           float hv[1] = {e[0] * Hin[0]};
 #pragma unroll
@@ -767,7 +786,7 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
     int exz;
     {
       const float wt = rw.at(rw.cw, 0);
-      const float gt = VJP ? rw.at(rw.cg, 0) : 0.f;
+      const float gt = VJP ? rw.at(rw.cg, 0) : 0.f, mf = rw.at(rw.cm, 0);
       const float noff = rw.at(rw.cf, 0) - (float)off;
       const float* const rd = vb + par * PL * GS;
       float sv[2] = {0.f, 0.f};
@@ -783,7 +802,7 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
             const float d = fmaf(nkap, cc[i][j][b], wt);
             const float e = ex2(fmaf(-d, d, noff));
             sv[0] = fmaf(e, Hin[b], sv[0]);
-            if constexpr (VJP) sv[1] = fmaf(e, fmaf(-gt * d, Hin[b], Bin[b]), sv[1]);
+            if constexpr (VJP) sv[1] = fmaf(e, fmaf(-gt * (d - mf), Hin[b], Bin[b]), sv[1]);
           }
         }
         asm volatile("" ::: "memory");
@@ -834,9 +853,12 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
       }
       float wt = rw.at(rw.cw, t);
       float gt = VJP ? rw.at(rw.cg, t) : 0.f;
-      lin::to_vgpr(wt, gt);
+      float mf = rw.at(rw.cm, t);
+      lin::to_vgpr(wt, gt, mf);
       const float noff = rw.at(rw.cf, t) - (float)off;
-      const float sc = ldexpf(rz, exz - (ex - off) - rw.at_i(ec, t));
+      const int es = exz - (ex - off) - rw.at_i(ec, t);
+      if (es > lin::kScaleMax) bad = true;
+      const float grz = gt * rz, drz = dws * rz;
       const float* const rd = vb + par * PL * GS;
       float* const wr = vb + (par ^ 1) * PL * GS;
       const int tn = t + 1 < L ? t + 1 : t;
@@ -860,8 +882,8 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
         float Hc[K], Bc[K];
 #pragma unroll
         for (int u = 0; u < K; ++u) {
-          Hc[u] = pH[u] * sc;
-          Bc[u] = VJP ? pB[u] * sc : 0.f;
+          Hc[u] = ldexpf(pH[u], es);
+          Bc[u] = VJP ? ldexpf(pB[u], es) : 0.f;
         }
         {  // the next super-group's history row (the next step's first after the last)
           const bool last = i + 1 >= SGT;
@@ -871,11 +893,12 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
         float gov[K], aov[K];
 #pragma unroll
         for (int u = 0; u < K; ++u) {
-          float al[K], qq[K], dd[K];
+          float al[K], qq[K], dd[K], dw[K];  // d about the edge of the range, and about the weight
 #pragma unroll
           for (int j = 0; j < K; ++j) {
-            dd[j] = fmaf(nkap, cc[i][j][u], wtl);
-            const float e = ex2(fmaf(-dd[j], dd[j], noff));
+            dw[j] = fmaf(nkap, cc[i][j][u], wtl);
+            dd[j] = dw[j] - mf;
+            const float e = ex2(fmaf(-dw[j], dw[j], noff));
             al[j] = e * Gin[j];
             if constexpr (VJP) qq[j] = e * fmaf(-gG[j], dd[j], Ain[j]);
           }
@@ -905,10 +928,10 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
             m[VJP ? 3 : 0] = fmaf(sad, bx, fmaf(Hu, sqd, m[VJP ? 3 : 0]));
             if constexpr (DC) {
               // p (g + d (X - E X) / (kappa^2 T)) of the group's K states
-              const float aq = Hu * gt, bq = bx * dws, cq = Hu * dws;
+              const float aq = Hu * grz, bq = bx * drz, cq = Hu * drz;
 #pragma unroll
               for (int j = 0; j < K; ++j) {
-                acc[i][j][u] = fmaf(dd[j], fmaf(al[j], bq, qq[j] * cq), fmaf(al[j], aq, acc[i][j][u]));
+                acc[i][j][u] = fmaf(dw[j], fmaf(al[j], bq, qq[j] * cq), fmaf(al[j], aq, acc[i][j][u]));
                 pin(acc[i][j][u]);  // (or it sinks below the barrier, its inputs live across)
               }
             }
@@ -919,7 +942,9 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
         if constexpr (VJP) st_vec<K>(wr + GS + (tb + i * TPB) * K, aov);
         asm volatile("" ::: "memory");
       }
-      const int q = (int)(t & (Q - 1));
+#pragma unroll
+      for (int c = 0; c < NM; ++c) m[c] *= rz;
+      const int q = t & (Q - 1);
       if constexpr (HALF) {
 #pragma unroll
         for (int c = 0; c < NM; ++c) m[c] += dpp<0xB1>(m[c]);
@@ -952,7 +977,7 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
         }
         if constexpr (MW) {
           if (wave == 0) {
-            const float ws = __shfl(rw.cw, t0 - rw.base + (ln & (Q - 1)));
+            const float ws = __shfl(rw.cw - rw.cm, t0 - rw.base + (ln & (Q - 1)));
             if (ln < Q) {
               ld_vec<NM>(wsum + (par * NW * Q + ln) * NM, r);
 #pragma unroll
@@ -967,7 +992,7 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
           }
         } else {
           const int ts = t0 + (ln & (W - 1)) / (W / Q);
-          const float ws = __shfl(rw.cw, (ln & ~(W - 1)) + ts - rw.base);
+          const float ws = __shfl(rw.cw - rw.cm, (ln & ~(W - 1)) + ts - rw.base);
           if (ts < L && valid && (ln & (W - 1)) % (W / Q) == 0) lin::step_outputs<VJP>(a, bb * L + ts, ws, r, bad);
         }
       }

@@ -402,9 +402,19 @@ __device__ __forceinline__ void st_pair_at(uint32_t addr, float a, float b) {
   *reinterpret_cast<lds_f2*>(addr) = v;
 }
 
-constexpr int kTopExp = 50;                  // a rescale puts the largest entry at 2^50
-constexpr float kTop = 0x1p50f;
-constexpr float kFarMax = 512.f;             // log2 units of a weight's distance outside the codebook
+// a rescale puts the largest entry at 2^50 (products alpha H stay in range);
+// with dCodebook at 2^90, H taking the exponents of both vectors and Z before
+// it meets alpha
+constexpr int top_exp(bool dc) { return dc ? 90 : 50; }
+constexpr float floor_of(bool dc) { return dc ? 0x1p-36f : 0x1p-30f; }
+constexpr float ceil_of(bool dc) { return dc ? 0x1p116f : 0x1p100f; }
+constexpr float top(bool dc) { return dc ? 0x1p90f : 0x1p50f; }
+// FbArgs::far_max is the square of a weight's distance outside the codebook,
+// in log2 units, up to which a step's exponents leave it out; beyond, the
+// block is marked.  Moments about the weight round at 6e-8 of that square (dW
+// at w = 40, T = 0.05: 1.7e-4 off), so without dCodebook it is 64, and 24
+// below T = 0.04, where the double-float pass does better; with dCodebook,
+// whose moments are about the edge of the range, 4096.
 
 // e with x = m 2^e, 1 <= m < 2, for a positive normal x (-127 for zero or a
 // denormal, 128 for inf or NaN)
@@ -524,10 +534,9 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
     chi = read_lane(mm[1] * (DC ? kap : 1.f), 0);
     __syncthreads();
   }
-  auto far2 = [&](float w) {
-    const float d = fmaxf(0.f, fmaxf(w - chi, clo - w));
-    return d * d;
-  };
+  auto beyond = [&](float w) { return w - fminf(fmaxf(w, clo), chi); };
+  // (whole log2 units: both sweeps take out the same)
+  auto far2 = [&](float m) { return floorf(m * m); };
 
   for (int64_t base = blockIdx.x; base < a.B; base += gridDim.x) {
     if constexpr (DC) load_cbr();
@@ -551,9 +560,9 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
     // ------------------------------------------------------------------ S0
     // Backward: H and the unnormalised tangent H B in the pair slots, in
     // place; H_{L-1} = 1 is stored as 2^50.
-    for (int i = threadIdx.x; i < 2 * GS; i += NT) lds[i] = (i & 1) ? 0.f : rot::kTop;
+    for (int i = threadIdx.x; i < 2 * GS; i += NT) lds[i] = (i & 1) ? 0.f : rot::top(DC);
     __syncthreads();
-    int ex = rot::kTopExp;  // exponent of the vector being read
+    int ex = rot::top_exp(DC);  // exponent of the vector being read
     int off = 0;            // its rescale, folded into this step's exponentials
     float lz2 = 0.f, xbar = 0.f;
     float far = 0.f;        // what the exponents leave out
@@ -575,8 +584,9 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
         wnx = ld_uniform(wbu, tn);
         if constexpr (VJP) gnx = ld_uniform(gbu, tn);
       }
-      const float f2 = far2(wt);
-      if (!(f2 <= rot::kFarMax)) bad = true;
+      const float mf = beyond(wt);
+      const float f2 = far2(mf);
+      if (!(f2 <= a.far_max)) bad = true;
       far += f2;
       const float noff = f2 - (float)off;
       const uint32_t rs = __builtin_amdgcn_readfirstlane(r2);
@@ -606,7 +616,7 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
               const float d = diff(cbr[i][j][b], wtl);
               const float e = ex2(fmaf(-d, d, noff));
               ls = fmaf(e, Hin[b], ls);
-              if constexpr (VJP) ly = fmaf(e, fmaf(-gt * d, Hin[b], Bin[b]), ly);
+              if constexpr (VJP) ly = fmaf(e, fmaf(-gt * (DC ? d - mf : d), Hin[b], Bin[b]), ly);
             }
           }
           asm volatile("" ::: "memory");
@@ -653,6 +663,9 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
           for (int b = 0; b < K; ++b) {
             d[b] = diff(cbr[i][j][b], wtl);
             e[b] = ex2(fmaf(-d[b], d[b], noff));
+            // with dCodebook a weight outside the codebook's range has its tangent
+            // terms and moments about the edge: d - mf keeps the codewords' differences
+            if constexpr (DC) d[b] -= mf;
           }
           float hv0 = e[0] * Hin[0];
 #pragma unroll
@@ -683,8 +696,8 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
       red_post<1, 1u>(vmax, rc);
       ex -= off;  // the exponent of what this step wrote
       if (threadIdx.x == 0) sm_eH[t - 1] = (float)ex;
-      if (!(vmax[0] >= 0x1p-30f && vmax[0] <= 0x1p100f)) bad = true;
-      off = bad ? 0 : rot::exp_of(vmax[0]) - rot::kTopExp;
+      if (!(vmax[0] >= rot::floor_of(DC) && vmax[0] <= rot::ceil_of(DC))) bad = true;
+      off = bad ? 0 : rot::exp_of(vmax[0]) - rot::top_exp(DC);
       r2 = r2 == 0 ? 12u : r2 - 2u;
     }
 
@@ -692,11 +705,11 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
     // Forward: G and the unnormalised tangent G A in the pair slots, in
     // place; G_0 = 1 stored as 2^50.  A is centred on g_{t-1} w_soft_{t-1}
     // when it is read (G A - c G).
-    for (int i = threadIdx.x; i < 2 * GS; i += NT) lds[i] = (i & 1) ? 0.f : rot::kTop;
+    for (int i = threadIdx.x; i < 2 * GS; i += NT) lds[i] = (i & 1) ? 0.f : rot::top(DC);
     __syncthreads();
     const float dws = a.dws;
     float cprev = 0.f;
-    ex = rot::kTopExp;
+    ex = rot::top_exp(DC);
     off = 0;
     float acc[DC ? SGT : 1][K][K];   // dCodebook of the block
     float p0[K][K];                  // codebook rows of the next super-group, one ahead
@@ -731,14 +744,19 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
         if constexpr (VJP) gnx = ld_uniform(gbu, tn);
       }
       const float eHt = sm_eH[t];
-      const float noff = far2(wt) - (float)off;
+      const float mf = beyond(wt);
+      const float noff = far2(mf) - (float)off;
       // dCodebook's marginals are alpha H / Z: the step's normalisation in
       // (g, 1 / (kappa^2 T)), known from the exponents before the step
       float gsc = 0.f, dsc = 0.f;
+      int es = 0;
       if constexpr (DC) {
-        const float sc = ldexpf(rz, exz - (ex - off) - (int)eHt);
-        gsc = gt * sc;
-        dsc = dws * sc;
+        es = exz - (ex - off) - (int)eHt;
+        // (the states' alpha H 200 log2 units below the largest entries' product:
+        // H times the scale could leave the range elsewhere)
+        if (es > 20) bad = true;
+        gsc = gt * rz;
+        dsc = dws * rz;
       }
       const uint32_t rs = __builtin_amdgcn_readfirstlane(r2);
       const uint32_t tslot = rot::slot8(phtb, rs);
@@ -770,8 +788,8 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
         float Hc[K], Bc[K];
 #pragma unroll
         for (int u = 0; u < K; ++u) {
-          Hc[u] = pH[u];
-          Bc[u] = VJP ? pB[u] : 0.f;
+          Hc[u] = DC ? ldexpf(pH[u], es) : pH[u];
+          Bc[u] = DC ? ldexpf(pB[u], es) : VJP ? pB[u] : 0.f;
         }
         float cc[K][K];
 #pragma unroll
@@ -795,11 +813,12 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
           if constexpr (VJP) {
             // per input j: alpha = e G and q = e (G A - g_t G d), the state's
             // unnormalised tangent with the step's term g_t (c - w_t) = -g_t d
-            float al[K], q[K], dd[K];
+            float al[K], q[K], dd[K], dw[K];
   #pragma unroll
             for (int j = 0; j < K; ++j) {
-              dd[j] = diff(cc[j][u], wtl);
-              const float e = ex2(fmaf(-dd[j], dd[j], noff));
+              dw[j] = diff(cc[j][u], wtl);
+              dd[j] = DC ? dw[j] - mf : dw[j];
+              const float e = ex2(fmaf(-dw[j], dw[j], noff));
               al[j] = e * Gin[j];
               q[j] = e * fmaf(-gG[j], dd[j], Ain[j]);
             }
@@ -823,7 +842,7 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
               const float aq = Hu * gsc, bq = bx * dsc, cq = Hu * dsc;
 #pragma unroll
               for (int j = 0; j < K; ++j) {
-                acc[i][j][u] = fmaf(dd[j], fmaf(al[j], bq, q[j] * cq), fmaf(al[j], aq, acc[i][j][u]));
+                acc[i][j][u] = fmaf(dw[j], fmaf(al[j], bq, q[j] * cq), fmaf(al[j], aq, acc[i][j][u]));
                 pin(acc[i][j][u]);  // (or it sinks below the barrier, its inputs live across)
               }
             }
@@ -854,16 +873,20 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
       const float r1 = 1.f / rv[2];
       const float md = rv[1] * r1;   // E_p[w' - c'] = w'_t - w_soft'_t
       if (threadIdx.x == 0) {
-        if (a.w_soft) a.w_soft[bb * L + t] = (wt - md) * a.inv_kap;
+        if (a.w_soft) a.w_soft[bb * L + t] = ((DC ? wt - mf : wt) - md) * a.inv_kap;
         // dW = Cov_p(X, c') / (kappa^2 T), Cov_p(X, c') = -E[(X - xbar) d] + E[X - xbar] E[d]
         if (VJP && a.dW) a.dW[bb * L + t] = fmaf(rv[VJP ? 3 : 0] * r1, rv[1], -rv[VJP ? 4 : 0]) * r1 * dws;
       }
       // the step's mass sum_s alpha_t beta_t must equal Z
-      const float lzt = lg2(rv[2]) - (float)(ex - off) - eHt;
-      if (!(fabsf(lzt - lz2) <= 2e-4f)) bad = true;
-      if (!(rv[0] >= 0x1p-30f && rv[0] <= 0x1p100f)) bad = true;
+      if constexpr (DC) {
+        if (!(fabsf(rv[2] * rz - 1.f) <= 1.4e-4f)) bad = true;
+      } else {
+        const float lzt = lg2(rv[2]) - (float)(ex - off) - eHt;
+        if (!(fabsf(lzt - lz2) <= 2e-4f)) bad = true;
+      }
+      if (!(rv[0] >= rot::floor_of(DC) && rv[0] <= rot::ceil_of(DC))) bad = true;
       ex -= off;
-      off = bad ? 0 : rot::exp_of(rv[0]) - rot::kTopExp;
+      off = bad ? 0 : rot::exp_of(rv[0]) - rot::top_exp(DC);
       // the step's term of A moves from g_t (c - w_t) to g_t (c - w_soft_t)
       // when it is read; E_p[X_{t+1}] = E_p[X_t] - g_t (w_soft_t - w_t)
       if constexpr (VJP) {
