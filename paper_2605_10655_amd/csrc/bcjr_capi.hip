@@ -531,7 +531,7 @@ int run_fb_hp(const float* w, int64_t B, int64_t L, const float* codebook, int n
 // S = 65536, k = 2 at T <= 0.015: the sum-product and VJP over the states
 // within kPrunedMargin nats of the block's best path (bcjr_pruned_kernels.h).
 // Workspace: [block flags][fp64 dCodebook accumulator][slots: min-sum bytes,
-// kept-state bits, step minima, best cost, kept-state entries].  Blocks are
+// later kept-state entries; kept-state bits, step minima, best cost].  Blocks are
 // taken in chunks of one slot each; a block the pruned kernel cannot finish
 // (more kept state-steps than its slot holds, or no finite logZ) is marked
 // and recomputed afterwards by the double-float kernel in its repair mode,
@@ -562,7 +562,9 @@ PrLayout pr_layout(int64_t L) {
   l.hmin = align_up((size_t)L * sizeof(float));
   l.best = align_up(sizeof(float));
   l.ent = align_up((size_t)2 * l.ecap * sizeof(double));
-  l.slot = l.q + l.bm + l.hmin + l.best + l.ent;
+  // (a block's bound bytes are read for the last time before its entries are
+  // written: they share memory, 2 x 1024 doubles against 16384 bytes per step)
+  l.slot = std::max(l.q, l.ent) + l.bm + l.hmin + l.best;
   return l;
 }
 
@@ -620,11 +622,11 @@ int run_fb_pruned(const float* w, int64_t B, int64_t L, const float* codebook, i
   a.theta = (float)(2.0 * (double)T * kPrunedMargin);
   a.qscale = (float)(16.0 / (2.0 * (double)T * kPrunedMargin));
   char* p = base;
-  a.q = reinterpret_cast<uint8_t*>(p);   p += (size_t)slots * lay.q;
+  a.q = reinterpret_cast<uint8_t*>(p);
+  a.ent = reinterpret_cast<double*>(p);  p += (size_t)slots * std::max(lay.q, lay.ent);
   a.bm = reinterpret_cast<uint64_t*>(p); p += (size_t)slots * lay.bm;
   a.hmin = reinterpret_cast<float*>(p);  p += (size_t)slots * lay.hmin;
-  a.best = reinterpret_cast<float*>(p);  p += (size_t)slots * lay.best;
-  a.ent = reinterpret_cast<double*>(p);
+  a.best = reinterpret_cast<float*>(p);
   a.ecap = lay.ecap;
   a.dc = dcacc;
   a.w_soft = w_soft; a.logZ = logZ; a.dW = dW;
@@ -1234,8 +1236,12 @@ int run_block_ldl(const float* H, int64_t d, int64_t b, double damp, double* M, 
                          stream, A, d, p, w);
     }
   }
-  hipLaunchKernelGGL(ldl::rinv_kernel, dim3((unsigned)(d / b)), dim3(256), 0, stream, (const double*)A, d,
-                     b, Rinv);
+  if (b <= ldl::kRinvMaxB)
+    hipLaunchKernelGGL(ldl::rinv_kernel, dim3((unsigned)(d / b * ((b + 3) / 4))), dim3(256),
+                       (size_t)4 * b * sizeof(double), stream, (const double*)A, d, b, Rinv);
+  else
+    hipLaunchKernelGGL(ldl::rinv_large_kernel, dim3((unsigned)(d / b)), dim3(256), 0, stream, (const double*)A,
+                       d, b, Rinv);
   hipLaunchKernelGGL(ldl::m_kernel, dim3(blocks_for(d * d, 256)), dim3(256), 0, stream, (const double*)A, d,
                      b, (const double*)Rinv, M);
   if (D)

@@ -192,6 +192,9 @@ __device__ __forceinline__ void lse_merge(double& m, double& s, double& y, doubl
 // wave only, whose memory operations take effect in program order: a fence
 // at wavefront scope keeps the compiler from reordering them and emits no
 // wait.
+// a value that is uniform, held in a vector register all the same
+__device__ __forceinline__ void to_vgpr(float& x) { asm volatile("" : "+v"(x)); }
+
 __device__ __forceinline__ void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); }
 
 // state of bit `bit` of word `q`
@@ -231,7 +234,8 @@ __global__ void __launch_bounds__(pr::NT) mm_back_kernel(PrArgs a) {
     for (int64_t t = L - 1; t >= 0; --t) {
       const float* pin = lds_mm + (t & 1) * GS;
       float* pout = lds_mm + ((t + 1) & 1) * GS;
-      const float wt = ld_uniform(wb, t);
+      float wt = ld_uniform(wb, t);
+      to_vgpr(wt);  // (in a vector register: with a scalar operand a subtraction issues at half rate)
       float in[SGT][K];
       float mn = INFINITY;
 #pragma unroll
@@ -244,12 +248,13 @@ __global__ void __launch_bounds__(pr::NT) mm_back_kernel(PrArgs a) {
       for (int i = 0; i < SGT; ++i)
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-          float m = INFINITY;
+          float f[K];
 #pragma unroll
           for (int b = 0; b < K; ++b) {
             const float d = wt - cb[i][j][b];
-            m = fminf(m, fmaf(d, d, in[i][b]));
+            f[b] = fmaf(d, d, in[i][b]);
           }
+          const float m = fminf(fminf(f[0], f[1]), fminf(f[2], f[3]));
           // (at t = 0 these are the best path costs through each state;
           // the half no later step reads holds them)
           pout[j * NSG + tb + i * NT] = m;
@@ -325,7 +330,7 @@ __global__ void __launch_bounds__(pr::NT) mm_fwd_kernel(PrArgs a) {
     for (int64_t t = 0; t < L; ++t) {
       const float* pin = lds_mm + (t & 1) * GS;
       float* pout = lds_mm + ((t + 1) & 1) * GS;
-      const float wt = wn;
+      float wt = wn;
       const float lmh = lim - hn;
       uint32_t qc[SGT];
 #pragma unroll
@@ -339,6 +344,7 @@ __global__ void __launch_bounds__(pr::NT) mm_fwd_kernel(PrArgs a) {
         wn = ld_uniform(wb, tn);
         hn = ld_uniform(hmin, tn);
       }
+      to_vgpr(wt);
       uint32_t mask[2] = {0u, 0u};
 #pragma unroll
       for (int i = 0; i < SGT; ++i) {
@@ -348,22 +354,27 @@ __global__ void __launch_bounds__(pr::NT) mm_fwd_kernel(PrArgs a) {
         for (int j = 0; j < K; ++j) gin[j] = pin[j * NSG + sg];
         const uint32_t qw = qc[i];
         float mo[K];
-        uint32_t bits = 0;
+        float f[K][K], thr[K];
 #pragma unroll
         for (int u = 0; u < K; ++u) {
           // (the forward cost a kept state may reach: one subtraction for
           // the four states of this bound, inside the window's widening)
-          const float thr = lmh - bval[(qw >> (8 * u)) & 0xFFu];
-          float m = INFINITY;
+          thr[u] = lmh - bval[(qw >> (8 * u)) & 0xFFu];
 #pragma unroll
           for (int j = 0; j < K; ++j) {
             const float d = wt - cb[i][j][u];
-            const float f = fmaf(d, d, gin[j]);
-            m = fminf(m, f);
-            bits |= (f <= thr ? 1u : 0u) << (j * 4 + u);
+            f[j][u] = fmaf(d, d, gin[j]);
           }
-          mo[u] = m;
+          mo[u] = fminf(fminf(f[0][u], f[1][u]), fminf(f[2][u], f[3][u]));
         }
+        // bit j * 4 + u: the sign of thr - f (set above the threshold) shifted in
+        // from bit 15 down, one full-rate subtraction and one shift per state where
+        // a compare, a select and an or took two and a half half-rate instructions
+        uint32_t over = 0;
+#pragma unroll
+        for (int x = K * K - 1; x >= 0; --x)
+          over = __builtin_amdgcn_alignbit(over, as_u(thr[x & 3] - f[x >> 2][x & 3]), 31);
+        uint32_t bits = ~over & 0xFFFFu;
         // (after the last step this row goes to the buffer half no later
         // step reads; the next block clears it behind the step's barrier)
         *reinterpret_cast<float4*>(pout + sg * K) = make_float4(mo[0], mo[1], mo[2], mo[3]);
@@ -582,27 +593,14 @@ __global__ void __launch_bounds__(pr::SP_WAVES * 64, 2) pruned_sp_kernel(PrArgs 
             const int64_t e = base + r0 + k;
             const double cs = (double)a.c[s];
             const double h = -(wt - cs) * (wt - cs) * i2T;
-            double lv, av;
-            if (t == 0) {
-              lv = h;
-              av = gt * cs;
-            } else {
-              // predecessors (s >> 2) + j 2^14: one word, bits ip * 16 + j * 4 + up
-              int qp, b0;
-              pos_of(s >> 2, qp, b0);  // (j = 0)
-              const uint64_t word = nbm[qp];
-              const uint32_t pr0 = npre[qp];
-              double pm = -INFINITY, ps = 0.0, py = 0.0;
-#pragma unroll
-              for (int j = 0; j < K; ++j) {
-                const int pb = b0 + j * 4;
-                if ((word >> pb) & 1ull) {
-                  const int64_t ep = base_prev + pr0 + __popcll(word & ((1ull << pb) - 1ull));
-                  lse_add(pm, ps, py, la[ep], aa[ep]);
-                }
-              }
-              lv = (pm > -INFINITY) ? h + pm + (ps == 1.0 ? 0.0 : log(ps)) : -INFINITY;
-              av = gt * cs + ((pm > -INFINITY) ? py / ps : 0.0);
+            // (all four predecessors' entries are loaded before any is used)
+            double lv = h, av = gt * cs;
+            if (t > 0) {
+              double v[K], y[K], lp, mp;
+              pred_vals(s, nbm, npre, base_prev, la, aa, v, y);
+              lse4(v, y, lp, mp);
+              lv = h + lp;
+              av += mp;
             }
             la[e] = lv;
             aa[e] = av;
@@ -691,25 +689,9 @@ __global__ void __launch_bounds__(pr::SP_WAVES * 64, 2) pruned_sp_kernel(PrArgs 
             const double lae = la[e], aae = aa[e];
             double lbv = 0.0, bvv = 0.0;
             if (t + 1 < L) {
-              // successors (s mod 2^14) * 4 + b: one word, bits id * 16 + jd * 4 + b
-              const int s14 = s & (GS - 1);
-              int qd, b0;
-              pos_of(s14 << 2, qd, b0);  // (b = 0)
-              const uint64_t word = nbm[qd];
-              const uint32_t pr0 = npre[qd];
-              double nm = -INFINITY, ns = 0.0, ny = 0.0;
-#pragma unroll
-              for (int b = 0; b < K; ++b) {
-                const int nb = b0 + b;
-                if ((word >> nb) & 1ull) {
-                  const int64_t ed = base_next + pr0 + __popcll(word & ((1ull << nb) - 1ull));
-                  const double cd = (double)a.c[(s14 << 2) | b];
-                  const double hd = -(wn - cd) * (wn - cd) * i2T;
-                  lse_add(nm, ns, ny, hd + la[ed], gn * cd + aa[ed]);  // (step t + 1: beta, B)
-                }
-              }
-              lbv = (nm > -INFINITY) ? nm + (ns == 1.0 ? 0.0 : log(ns)) : -INFINITY;
-              bvv = (nm > -INFINITY) ? ny / ns : 0.0;
+              double v[K], y[K];
+              succ_vals(s, nbm, npre, base_next, la, aa, a.c, wn, gn, i2T, v, y);
+              lse4(v, y, lbv, bvv);
             }
             la[e] = lbv;
             aa[e] = bvv;
