@@ -266,13 +266,13 @@ FbFn fb_pick(int n, int k, const Family& f, bool vjp, bool dc) {
 
 template <int KB>
 VitFn vit_pick_kb(int n, const Family& f) {
-  if (f.sgmax == 1) return viterbi_kernel<KB, 0, 1, 256>;
+  if (f.sgmax == 1) return viterbi_kernel<KB, 0, 1, 256, false>;
   if constexpr (KB < 3) {
     constexpr int n512 = 2 * KB + 9;
-    if (n == n512) return viterbi_kernel<KB, n512, 2, 256>;
-    if (n == n512 + 1) return viterbi_kernel<KB, n512 + 1, 4, 256>;
-    if (n == n512 + 2) return viterbi_kernel<KB, n512 + 2, 8, 256>;
-    if (n == n512 + 3) return viterbi_kernel<KB, n512 + 3, 4, 1024>;
+    if (n == n512) return viterbi_kernel<KB, n512, 2, 256, false>;
+    if (n == n512 + 1) return viterbi_kernel<KB, n512 + 1, 4, 256, false>;
+    if (n == n512 + 2) return viterbi_kernel<KB, n512 + 2, 8, 256, false>;
+    if (n == n512 + 3) return viterbi_kernel<KB, n512 + 3, 4, 1024, false>;
   }
   return nullptr;
 }
@@ -287,6 +287,13 @@ VitFn vit_pick(int n, int k, const Family& f) {
 }
 
 // the fp32 min-sum decode of the centring reference, same families
+// the MIN form of the shapes of 4096 super-groups
+VitFn vit_min_pick(int n, int k) {
+  if (k == 2 && n == 16) return viterbi_kernel<2, 16, 4, 1024, true>;
+  if (k == 1 && n == 14) return viterbi_kernel<1, 14, 4, 1024, true>;
+  return nullptr;
+}
+
 template <int KB>
 VitFn vit_ref_pick_kb(int n, const Family& f) {
   if (f.sgmax == 1) return viterbi_ref_kernel<KB, 0, 1, 256>;
@@ -446,6 +453,17 @@ int run_viterbi(const float* w, int64_t B, int64_t L, const float* codebook, int
   a.states = states; a.w_hard = w_hard;
   a.flags = approx ? flags : nullptr;
   a.bp = static_cast<uint8_t*>(workspace);
+  // The MIN form saves 0.27 us a step at 65536 states; its second launch and
+  // the looks over the codebook cost about 10 us: from 256 steps in a row on.
+  const VitFn fmin = approx ? nullptr : vit_min_pick(n, k);
+  if (fmin && ceil_div(B, grid * f.bpw) * L >= 256) {
+    int e2 = 0;
+    const int64_t gmin = grid_size((const void*)fmin, f, lds, B, ws_bytes, slot, &e2);  // (sets its LDS size too)
+    if (e2) return BCJR_ERR_HIP;
+    a.scan = 1;
+    hipLaunchKernelGGL(fmin, dim3((unsigned)(gmin < grid ? gmin : grid)), dim3(f.nt), lds, stream, a);
+    if (hipGetLastError() != hipSuccess) return BCJR_ERR_HIP;
+  }
   hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(f.nt), lds, stream, a);
   return hipGetLastError() == hipSuccess ? BCJR_OK : BCJR_ERR_HIP;
 }
@@ -667,7 +685,10 @@ int reduce_dc(const double* part, int64_t slots, int64_t S, float* out, hipStrea
 
 // The linear-domain kernels below 65536 states (bcjr_lin_kernels.h): the soft
 // codeword to the field scale of the 65536-state one, the VJP, with or
-// without dCodebook, where fp32 log vectors serve it (T >= 0.04).
+// without dCodebook, where fp32 log vectors serve it (T >= 0.04): S = 4096 with
+// dCodebook 20.3 ms against 41.1 in the log domain (16384 blocks, T = 0.1);
+// below, dCodebook in fp32 sums (tried at 65536 states) is 1.3e-6 to 2.7e-6 off where the double-float
+// kernel is 4e-7.
 bool lin_small_ok(int n, int k, float T, bool vjp) {
   if (!supported(n, k) || (n == 16 && k == 2)) return false;
   return vjp ? !use_high_precision(T) : 1.4426950408889634074 / (2.0 * (double)T) <= kLinearK2;
@@ -853,7 +874,8 @@ int run_fb(const float* w, int64_t B, int64_t L, const float* codebook, int n, i
     return run_gen(w, B, L, codebook, n, k, T, g, w_soft, logZ, dW, dCodebook, workspace, ws_bytes,
                    stream, vjp);
   // with dCodebook only where the log-domain fp32 kernel would serve too: below
-  // T = 0.04 single blocks' dCodebook is up to 2e-4 off in fp32 sums
+  // T = 0.04 single blocks' dCodebook is up to 2e-4 off in fp32 sums; above,
+  // 2048 blocks at T = 0.1 take 35.0 ms here and 57.8 in fb_kernel
   if (linear_ok(n, k, T) && (!dCodebook || !use_high_precision(T))) {
     const int st = run_fb_lin(w, B, L, codebook, n, k, T, g, w_soft, logZ, dW, dCodebook, workspace, ws_bytes,
                               stream, vjp);

@@ -131,6 +131,7 @@ struct VitArgs {
   // fp32 decode (one block per workgroup): when set, only the blocks marked
   // 1 here are decoded (the centring reference of a repair pass)
   const int32_t* flags;
+  int scan;            // two launches, by whether every codeword is finite
 };
 
 }  // namespace bcjr

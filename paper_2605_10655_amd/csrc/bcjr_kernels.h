@@ -1449,13 +1449,23 @@ __device__ __forceinline__ void st_digits(uint8_t* p, const uint8_t (&arg)[K]) {
   }
 }
 
+// The Viterbi candidates, MIN form: the value by one v_min_f64 and the digit by
+// the compare and one select, where selecting the value too takes two more; the
+// kernel is bound by these half-rate instructions (65536 states, 16384 blocks
+// of 256: 76.6 -> 72.2 ms).  The minimum of a NaN and a number is the number,
+// where the compare keeps a NaN that came first, so a codebook with a
+// non-finite word is left to the select form.  (A NaN or infinite weight makes
+// all candidates of a step alike, for which both agree.)  With a.scan both
+// forms are launched, each looks over the codebook and one of them leaves at
+// once; both in one kernel cost the gain (a branch per super-group 77.4 ms, two
+// sweeps 84.2).
 __device__ __forceinline__ double min_d(double a, double b) {
   double r;
   asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));  // (fmin would first quiet both)
   return r;
 }
 
-template <int KB, int NB, int SGMAX, int NT>
+template <int KB, int NB, int SGMAX, int NT, bool MIN>
 __global__ void __launch_bounds__(NT) viterbi_kernel(VitArgs a) {
   constexpr int K = 1 << KB;
   extern __shared__ double ldsd[];
@@ -1481,6 +1491,14 @@ __global__ void __launch_bounds__(NT) viterbi_kernel(VitArgs a) {
   // codebook rows through a buffer descriptor, one super-group ahead
   const rsrc_t cbk = make_rsrc(a.c, (uint32_t)4 << n);
   const uint32_t voK = (uint32_t)tb << (KB + 2);
+  if constexpr (NT == 1024) {
+    if (a.scan) {
+      int fin = 1;
+#pragma unroll 8
+      for (int s = tid; s < 1 << n; s += NT) fin &= (__float_as_uint(a.c[s]) & 0x7F800000u) != 0x7F800000u;
+      if ((__syncthreads_and(fin) != 0) != MIN) return;
+    }
+  }
 
   for (int64_t base = (int64_t)blockIdx.x * BPW; base < a.B; base += (int64_t)gridDim.x * BPW) {
     const int64_t blk = base + bw;
@@ -1533,25 +1551,42 @@ __global__ void __launch_bounds__(NT) viterbi_kernel(VitArgs a) {
           }
           if (t < L - 1) {
             uint8_t arg[K];
+            if constexpr (MIN) {
 #pragma unroll
-            for (int u = 0; u < K; ++u) {
-              // (the value by one minimum instruction, the digit by the compare:
-              // three instructions per candidate where selecting both took four)
-              double best = 0.0;
-              int bj = 0;
+              for (int u = 0; u < K; ++u) {
+                double best = 0.0;
+                int bj = 0;
 #pragma unroll
-              for (int j = 0; j < K; ++j) {
-                const double d = wt - (double)cc[j][u];
-                const double v = __dadd_rn(__dmul_rn(d, d), Min[j]);
-                if (j == 0) {
-                  best = v;
-                } else {
-                  bj = v < best ? j : bj;
-                  best = min_d(best, v);
+                for (int j = 0; j < K; ++j) {
+                  const double d = wt - (double)cc[j][u];
+                  const double v = __dadd_rn(__dmul_rn(d, d), Min[j]);
+                  if (j == 0) {
+                    best = v;
+                  } else {
+                    bj = v < best ? j : bj;
+                    best = min_d(best, v);
+                  }
                 }
+                Mout[i][u] = best;
+                arg[u] = (uint8_t)bj;
               }
-              Mout[i][u] = best;
-              arg[u] = (uint8_t)bj;
+            } else {
+#pragma unroll
+              for (int u = 0; u < K; ++u) {
+                double best = 0.0;
+                int bj = 0;
+#pragma unroll
+                for (int j = 0; j < K; ++j) {
+                  const double d = wt - (double)cc[j][u];
+                  const double v = __dadd_rn(__dmul_rn(d, d), Min[j]);
+                  if (j == 0 || v < best) {
+                    best = v;
+                    bj = j;
+                  }
+                }
+                Mout[i][u] = best;
+                arg[u] = (uint8_t)bj;
+              }
             }
             // bp[t+1][sg*K + u] = winning j of G-entry (sg, u)
             st_digits<K>(bp + (t + 1) * GS + sg * K, arg);

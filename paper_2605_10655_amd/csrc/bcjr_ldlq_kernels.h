@@ -136,7 +136,8 @@ __device__ __forceinline__ double rget(const double* C, int64_t d, int64_t i, in
 // are independent back substitutions; one wave takes one, its lanes the terms
 // of each row's sum (the row of R is contiguous, the column so far in LDS), and
 // d / b x b / 4 workgroups fill the chip.  With one thread per column the
-// serial sums took 4.3 ms of a 1024 x 1024 matrix's 27, now 0.3.
+// serial sums took 4.3 ms of a 1024 x 1024 call's 27.2 ms (whole call now
+// 20.7 ms).
 constexpr int64_t kRinvMaxB = 2048;  // (4 columns of doubles in 64 KiB)
 
 __global__ void __launch_bounds__(256) rinv_kernel(const double* C, int64_t d, int64_t b, double* Rinv) {

@@ -421,7 +421,7 @@ constexpr float top(bool dc) { return dc ? 0x1p90f : 0x1p50f; }
 __device__ __forceinline__ int exp_of(float x) { return (int)((__float_as_uint(x) >> 23) & 0xFFu) - 127; }
 }  // namespace rot
 
-// The same call (S = 65536, k = 2, fwd + w_soft + logZ + dW, no dCodebook) on
+// The same call (S = 65536, k = 2, fwd + w_soft + logZ + dW; DC: + dCodebook) on
 // the same rotating layout, workspace and history, with the group vectors
 // kept in the linear domain instead of the log domain:
 //   G_{t+1}(v) = sum_j e_t(j, v) G_t(j, v >> 2),  H_{t-1}(v) = sum_b e_t(v, b) H_t(...),
@@ -442,6 +442,12 @@ __device__ __forceinline__ int exp_of(float x) { return (int)((__float_as_uint(x
 // sum_s alpha_t beta_t departing from Z by more than 2e-4 log2 units -- is
 // marked in a.flags and recomputed by a second launch of the log-domain
 // (or, at field scales above 18, the double-float) kernel in repair mode.
+//
+// DC: the sums of the states a thread owns take, in the forward sweep, the
+// registers of its codebook rows, which then come from L2 one super-group
+// ahead.  2048 blocks of 256 at T = 0.1: 57.8 ms in fb_kernel, which stores
+// (G, A) for a third sweep (40 bytes of history per group-step, here 16),
+// 35.0 ms here; bound by the step's dependency chain at two waves per SIMD.
 template <int NT, bool VJP, bool DC>
 __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
   constexpr int KB = 2, K = 4, n = 16;

@@ -79,3 +79,51 @@ def test_vector_viterbi_tie_rule(n, B, L):
     np.testing.assert_array_equal(st, rst)
     np.testing.assert_array_equal(wh, c[st].reshape(B, L))
     assert np.any(O.maxmarginal_gap(w, c, n, 4, rst, V=2) == 0.0)
+
+
+def _strict_less_decode(w, c, n, k):
+    """Plain fp64 recursion: among the predecessors in order the first value,
+    then any strictly smaller one; a NaN that comes first stays."""
+    S, K = 1 << n, 1 << k
+    G = S >> k
+    cd = c.astype(np.float64)
+    out = np.zeros(w.shape, np.int64)
+    for b in range(w.shape[0]):
+        M = np.zeros(G)
+        digits = []
+        for t in range(w.shape[1]):
+            F = (float(w[b, t]) - cd) ** 2 + np.repeat(M, K)
+            if t == w.shape[1] - 1:
+                fin = np.where(F < np.inf, F, np.inf)
+                s = int(np.argmin(fin)) if np.isfinite(fin).any() else 0
+            else:
+                F = F.reshape(K, G)
+                M, d = F[0].copy(), np.zeros(G, np.int64)
+                for j in range(1, K):
+                    less = F[j] < M
+                    M, d = np.where(less, F[j], M), np.where(less, j, d)
+                digits.append(d)
+        for t in range(w.shape[1] - 1, -1, -1):
+            out[b, t] = s
+            if t:
+                v = s >> k
+                s = int((digits[t - 1][v] << (n - k)) | v)
+    return out
+
+
+@pytest.mark.parametrize("n,k", [(8, 2), (13, 2), (14, 1), (16, 2), (14, 3)])
+@pytest.mark.parametrize("bad", [None, "nan", "inf"])
+def test_scalar_viterbi_nonfinite_codewords(n, k, bad):
+    # equality is exact: the recursion is one square and one sum in fp64 on
+    # both sides (dyadic values, no rounding)
+    B, L = 2, 257 if (n, k) in ((14, 1), (16, 2)) else 7  # (the longer rows take the form with the minimum too)
+    w, c = dyadic(5 * n + k, B, L, 1 << n)
+    w[1, 2] = np.inf
+    if bad:
+        r = np.random.default_rng(n)
+        c[r.integers(0, 1 << n, 1 << (n - 3))] = np.nan if bad == "nan" else np.inf
+    _say(f"[ties] non-finite codewords n={n} k={k} {bad}")
+    with np.errstate(invalid="ignore"):
+        want = _strict_less_decode(w, c, n, k)
+    st, _ = P.viterbi_decode(dev(w), dev(c), n, k)
+    assert np.array_equal(host(st), want)
