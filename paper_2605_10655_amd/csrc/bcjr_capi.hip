@@ -834,8 +834,9 @@ int run_fb_lin(const float* w, int64_t B, int64_t L, const float* codebook, int 
   a.flags = flags;
   a.far_max = dc ? 4096.f : hp ? 24.f : 64.f;
   a.dc_part = part;
-  hipLaunchKernelGGL(scale_kernel, dim3((unsigned)ceil_div(S, 256)), dim3(256), 0, stream, codebook,
-                     a.kap, cs, S);
+  // (the gradient's powers of two land in the flags, one workgroup per 4 blocks)
+  hipLaunchKernelGGL(lin_prep_kernel, dim3((unsigned)(ceil_div(S, 256) + (vjp ? ceil_div(B, 4) : 0))), dim3(256), 0,
+                     stream, codebook, a.kap, cs, S, g, B, L, flags);
   if (hipGetLastError() != hipSuccess) return BCJR_ERR_HIP;
   a.histH = vjp ? nullptr : reinterpret_cast<float*>(base);
   a.histHB = vjp ? reinterpret_cast<float*>(base) : nullptr;

@@ -252,6 +252,21 @@ __device__ __forceinline__ void red_post(float (&v)[NQ], const RedCtx& r) {
   }
 }
 
+// The power of two e that the linear-domain VJPs take out of a block's upstream
+// gradient and put back at its outputs, from the block's largest |g|: sum |g_t|
+// 2^-e <= 1, so that no tangent is larger than a distance to the codebook.
+// Those kernels carry tangents times vectors near 2^50 or 2^90: with g as it
+// is (256 N(0, 1) entries times 2^x, 65536 states), dW was infinite from x = 13
+// (T = 1) or 24 (T = 0.05) up, and dCodebook lost its low terms from x = -30
+// down.  0 where there is nothing to
+// scale (no gradient, or an infinite one, whose block gets marked).
+__device__ __forceinline__ int grad_exp(float gmax, int64_t L) {
+  const uint32_t b = as_u(gmax);
+  if (b == 0u || b >= 0x7F800000u) return 0;
+  const int e = b < 0x00800000u ? -118 - __builtin_clz(b) : (int)(b >> 23) - 127;
+  return e + 1 + (L > 1 ? 64 - __builtin_clzll((unsigned long long)(L - 1)) : 0);
+}
+
 // (max, scaled sum) pairs: combine((m1,s1),(m2,s2)) = (M, s1 2^(m1-M) + s2 2^(m2-M))
 __device__ __forceinline__ void lse_pair(float& m, float& s, float mo, float so) {
   const float M = fmaxf(m, mo);

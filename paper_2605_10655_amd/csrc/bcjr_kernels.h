@@ -1408,6 +1408,26 @@ __global__ void scale_kernel(const float* c, float kap, float* cs, int64_t S) {
   if (i < S) cs[i] = c[i] * kap;
 }
 
+// The same, and in further workgroups the gradient's power of two of each block
+// (a wave per block), left in exps[B]: the linear-domain VJP of 65536 states
+// reads it there and leaves the block's flag in its place.
+__global__ void __launch_bounds__(256) lin_prep_kernel(const float* c, float kap, float* cs, int64_t S, const float* g,
+                                                       int64_t B, int64_t L, int32_t* exps) {
+  const int64_t nc = (S + 255) / 256;
+  if ((int64_t)blockIdx.x < nc) {
+    const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (s < S) cs[s] = c[s] * kap;
+    return;
+  }
+  const int64_t b = ((int64_t)blockIdx.x - nc) * 4 + (threadIdx.x >> 6);
+  if (b >= B) return;
+  float m = 0.f;
+#pragma unroll 4
+  for (int64_t i = threadIdx.x & 63; i < L; i += 64) m = fmaxf(m, fabsf(g[b * L + i]));
+  m = seg_reduce<true>(m, 64);
+  if ((threadIdx.x & 63) == 0) exps[b] = grad_exp(m, L);
+}
+
 // rows[r * stride + c] = v for r < nrows, c < row_len
 __global__ void fill_rows_kernel(float* rows, int64_t stride, int64_t nrows, int64_t row_len, float v) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

@@ -430,18 +430,19 @@ __device__ __forceinline__ int exp_of(float x) { return (int)((__float_as_uint(x
 // (G A and H B), so that a step needs one exponential per state and no
 // logarithm, maximum or reciprocal per group.  After each step the vector
 // is rescaled by an exact power of two that puts its largest entry at 2^50
-// (the exponent is folded into the next step's exponentials); fp32 then
-// holds every state within ~176 log2 units of the step's maximum at full
+// (with dCodebook 2^90; the exponent is folded into the next step's
+// exponentials); fp32 then holds every state within ~176 log2 units of the step's maximum at full
 // precision, where the states that carry the posterior lie within ~60-90
 // at T >= 0.04 on unit-variance data.  The marginals and the four dW moments
 // are products of the two sweeps' values, scale-invariant per step.
 //
 // A block whose vectors leave that range -- a step whose largest entry
 // falls below 2^-30 (a single-step decay of 80 log2 units, which the
-// posterior states would not survive) or the forward's per-step mass
-// sum_s alpha_t beta_t departing from Z by more than 2e-4 log2 units -- is
-// marked in a.flags and recomputed by a second launch of the log-domain
-// (or, at field scales above 18, the double-float) kernel in repair mode.
+// posterior states would not survive), the forward's per-step mass
+// sum_s alpha_t beta_t departing from Z by more than 2e-4 log2 units, or a
+// step's tangent moments not finite -- is marked in a.flags and recomputed by
+// a second launch of the log-domain (or, at field scales above 18, the
+// double-float) kernel in repair mode.
 //
 // DC: the sums of the states a thread owns take, in the forward sweep, the
 // registers of its codebook rows, which then come from L2 one super-group
@@ -551,6 +552,10 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
     const int64_t bbu = (int64_t)__builtin_amdgcn_readfirstlane((int)bb);
     const float* wbu = a.w + bbu * L;
     const float* gbu = VJP ? a.g + bbu * L : wbu;
+    // the power of two taken out of the block's gradient, left by lin_prep_kernel
+    // where the block's flag goes (with the loop for it in here the 16384-block
+    // call took 218.1 ms, this way 215.1: the compiler schedules the sweeps otherwise)
+    const int ge = VJP ? __builtin_amdgcn_readfirstlane(a.flags[bbu]) : 0;
     const rsrc_t hist = make_rsrc((VJP ? a.histHB : a.histH) + slot * L * hstep, (uint32_t)L * hstep * 4u);
     float* sm_eH = a.small + slot * 3 * L;  // exponent of the stored H_t: stored = true * 2^e
     bool bad = !lds_aligned;
@@ -565,7 +570,7 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
 
     // ------------------------------------------------------------------ S0
     // Backward: H and the unnormalised tangent H B in the pair slots, in
-    // place; H_{L-1} = 1 is stored as 2^50.
+    // place; H_{L-1} = 1 is stored as 2^50 (with dCodebook 2^90).
     for (int i = threadIdx.x; i < 2 * GS; i += NT) lds[i] = (i & 1) ? 0.f : rot::top(DC);
     __syncthreads();
     int ex = rot::top_exp(DC);  // exponent of the vector being read
@@ -582,7 +587,7 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
       const uint32_t vcH = tid_s * 4u;
       rc.red = red0 + ((L - 1 - t) & 1) * (NT / 64) * kRed;
       const float wt = wnx * kap;
-      float gt = gnx;
+      float gt = VJP ? ldexpf(gnx, -ge) : 0.f;
       // (in a vector register: a multiply with a scalar operand issues at half rate)
       if constexpr (VJP) pin(gt);
       {
@@ -709,8 +714,8 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
 
     // ------------------------------------------------------------------ S1
     // Forward: G and the unnormalised tangent G A in the pair slots, in
-    // place; G_0 = 1 stored as 2^50.  A is centred on g_{t-1} w_soft_{t-1}
-    // when it is read (G A - c G).
+    // place; G_0 = 1 stored as 2^50 (with dCodebook 2^90).  A is centred on
+    // g_{t-1} w_soft_{t-1} when it is read (G A - c G).
     for (int i = threadIdx.x; i < 2 * GS; i += NT) lds[i] = (i & 1) ? 0.f : rot::top(DC);
     __syncthreads();
     const float dws = a.dws;
@@ -742,7 +747,7 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
       const uint32_t voH_s = tid_s * K * 4u;
       rc.red = red0 + (t & 1) * (NT / 64) * kRed;
       const float wt = wnx * kap;
-      float gt = gnx;
+      float gt = VJP ? ldexpf(gnx, -ge) : 0.f;
       if constexpr (VJP) pin(gt);
       {
         const int64_t tn = t + 1 < L ? t + 1 : t;
@@ -881,7 +886,10 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
       if (threadIdx.x == 0) {
         if (a.w_soft) a.w_soft[bb * L + t] = ((DC ? wt - mf : wt) - md) * a.inv_kap;
         // dW = Cov_p(X, c') / (kappa^2 T), Cov_p(X, c') = -E[(X - xbar) d] + E[X - xbar] E[d]
-        if (VJP && a.dW) a.dW[bb * L + t] = fmaf(rv[VJP ? 3 : 0] * r1, rv[1], -rv[VJP ? 4 : 0]) * r1 * dws;
+        if (VJP && a.dW) a.dW[bb * L + t] = ldexpf(fmaf(rv[VJP ? 3 : 0] * r1, rv[1], -rv[VJP ? 4 : 0]) * r1 * dws, ge);
+      }
+      if constexpr (VJP) {
+        if (!(fabsf(rv[VJP ? 3 : 0]) + fabsf(rv[VJP ? 4 : 0]) < INFINITY)) bad = true;
       }
       // the step's mass sum_s alpha_t beta_t must equal Z
       if constexpr (DC) {
@@ -910,7 +918,7 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
           for (int j = 0; j < K; ++j) {
             double* const pj = part_at(i, j);
 #pragma unroll
-            for (int u = 0; u < K; ++u) pj[u] += (double)acc[i][j][u];
+            for (int u = 0; u < K; ++u) pj[u] += ldexp((double)acc[i][j][u], ge);
             asm volatile("" ::: "memory");
           }
       }

@@ -234,3 +234,41 @@ def test_linear_kernel_long_blocks_and_high_temperature(L, T):
     e_dw = grad_err(dW, rdW)
     print(f"  w_soft {e_ws:.2e} logZ {e_lz:.2e} dW {e_dw:.2e}", flush=True)
     assert e_ws <= TOL_WS and e_lz <= TOL_LOGZ and e_dw <= TOL_GRAD
+
+
+@pytest.mark.parametrize("want_dc", [False, True])
+@pytest.mark.parametrize("L,T", [(1, 0.1), (65, 0.05), (256, 0.2), (256, 1.0)])
+def test_linear_kernel_takes_any_gradient_scale(L, T, want_dc):
+    """The gradients are linear in g, and a power of two is taken out of every
+    block's g exactly: g times 2^x yields the same bits times 2^x (loss scales,
+    sums over many tokens; tiny ones), for the whole batch and, in dW, for
+    every block by itself.  The unscaled call is compared with the oracle, and
+    its flags show that no block needed the repair pass."""
+    c = WL.codebook(4)
+    r = np.random.Generator(np.random.PCG64(4900 + L))
+    w = r.standard_normal((3, L)).astype(np.float32)
+    g = r.standard_normal((3, L)).astype(np.float32)
+
+    def run(gr):
+        work = torch.full((P.bcjr_workspace_bytes(3, L, N, KB, P.OP_FWD_VJP),), 255, dtype=torch.uint8,
+                          device="cuda:0")
+        out = P.bcjr_soft_codeword_fwd_vjp(dev(w), dev(c), N, KB, T, dev(gr), want_dCodebook=want_dc,
+                                           workspace=work)
+        torch.cuda.synchronize()
+        assert work[4 << N:][:12].view(torch.int32).tolist() == [0, 0, 0]
+        return [x.cpu().numpy() for x in out[2:4] if x is not None]
+
+    print(f"linear kernel gradient scales: L={L} T={T} dc={want_dc}", flush=True)
+    base = run(g)
+    ref = O.soft_codeword_vjp(w, c, N, KB, float(np.float32(T)), g)[2:4]
+    for a, b in zip(base, ref):
+        assert grad_err(a, b) <= TOL_GRAD
+    for x in (-70, -30, 13, 17, 24, 44, 100):
+        for a, b in zip(run(np.ldexp(g, x)), base):
+            # (entries in the subnormal range on either side carry one rounding there)
+            np.testing.assert_allclose(a, np.ldexp(b, x), rtol=0, atol=2.0 ** (max(x, 0) - 149), err_msg=f"2^{x}")
+    rows = np.array([[-40], [0], [40]])
+    got, want = run(np.ldexp(g, rows))[0], np.ldexp(base[0], rows)
+    assert (np.abs(got - want) <= 2.0 ** (np.maximum(rows, 0) - 149)).all()
+    g[1] = 0.0
+    assert not run(g)[0][1].any()
