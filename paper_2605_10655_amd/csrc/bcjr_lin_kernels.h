@@ -33,8 +33,11 @@
 //
 // A block whose vectors leave the number range -- a step's largest entry
 // below a floor, the forward mass sum_s alpha_t beta_t / Z away from 1, a
-// weight far outside the codebook, anything not finite -- is marked in
-// a.flags and recomputed by a second launch of the log-domain kernels.
+// weight far outside the codebook, moments that are not finite -- is marked in
+// a.flags and recomputed by a second launch of the log-domain kernels.  The
+// tangents' range does not depend on the gradient's: a power of two per block
+// is taken out of g when its rows are read and put back at dW and dCodebook
+// (see grad_exp).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -84,14 +87,14 @@ constexpr bool tight(int n, int KB, int SGT) {
 }
 constexpr int batch(int n, int KB, int SGT) { return tight(n, KB, SGT) ? 2 : 4; }
 
-// LDS bytes of lin_sg_kernel: the ping-ponged vectors, the moments, and for
-// several waves their partial sums and maxima
+// LDS bytes of lin_sg_kernel: the ping-ponged vectors, the moments, for several
+// waves their partial sums and maxima, for several blocks their powers of two
 constexpr size_t sg_lds(int n, int KB, int SGT, bool VJP) {
   const size_t gs = (size_t)1 << (n - KB);
   const int tpb = (1 << (n - 2 * KB)) / SGT, waves = tpb > 64 ? tpb / 64 : 1, bpw = tpb > 64 ? 1 : 64 / tpb;
   return bpw * 2 * (VJP ? 2 : 1) * gs * 4 +
          (size_t)waves * batch(n, KB, SGT) * (tight(n, KB, SGT) ? 32 : 64) * (VJP ? 16 : 8) +
-         (waves > 1 ? (size_t)waves * (2 * batch(n, KB, SGT) * 16 + 2 * 4) : 0);
+         (waves > 1 ? (size_t)waves * (2 * batch(n, KB, SGT) * 16 + 2 * 4) : 0) + (bpw > 1 ? 4 * bpw : 0);
 }
 
 // A rescale puts the largest entry at 2^90.  A step may lower it to 2^-36 (a
@@ -172,6 +175,8 @@ struct Rows {
   int L;
   float kap, lo, hi;
   int li, seg0;          // lane in the segment, its first lane
+  int gs;                // the power of two taken out of g: a scalar (W = 64), or
+  int* gexp;             // each block's in LDS (a register less across the steps)
   float cw, cg, cf, cm, nw, ng;
   int base;
 
@@ -181,11 +186,34 @@ struct Rows {
     x = in ? w[i] : 0.f;
     if constexpr (VJP) y = in ? g[i] : 0.f;
   }
+  // from the row's largest |g|, four loads in flight (every lane of a block
+  // stores the same)
+  __device__ __forceinline__ void scale() {
+    float m = 0.f;
+    for (int b = 0; b < L; b += 4 * W) {
+      float y[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) y[q] = g[b + q * W + li < L ? b + q * W + li : L - 1];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) m = fmaxf(m, fabsf(y[q]));
+    }
+    const int e = grad_exp(seg_reduce<true>(m, W), L);
+    if constexpr (W == 64) {
+      gs = __builtin_amdgcn_readfirstlane(e);
+    } else {
+      gexp[lane_id() / W] = e;
+      wave_sync();
+    }
+  }
+  __device__ __forceinline__ int ge() const {
+    if constexpr (W == 64) return gs;
+    return gexp[lane_id() / W];  // (the lane index rebuilt: no register holds it)
+  }
   // takes the prefetched chunk as [b, b + W) and fetches the one at `next`
   __device__ __forceinline__ void take(int b, int next, bool& bad) {
     base = b;
     cw = nw * kap;
-    if constexpr (VJP) cg = ng;
+    if constexpr (VJP) cg = ldexpf(ng, -ge());
     cm = b + li < L ? beyond(cw, lo, hi) : 0.f;
     cf = floorf(cm * cm);  // (whole, so that both sweeps take out the same)
     if (!(cf <= kFarMax)) bad = true;
@@ -245,15 +273,17 @@ __device__ __forceinline__ void sum_batch(const float* m, int lane, float (&r)[N
 
 // w_soft_t and dW_t from a step's moments sum P d, sum P, sum P (X - E X),
 // sum P (X - E X) d (P normalised by Z: sum P is the forward mass); wt = w'_t, or the
-// edge of the range that the moments are about
+// edge of the range that the moments are about; ge: the power of two to put back
 template <bool VJP>
-__device__ __forceinline__ void step_outputs(const LinArgs& a, int64_t at, float wt, const float* r, bool& bad) {
+__device__ __forceinline__ void step_outputs(const LinArgs& a, int64_t at, float wt, int ge, const float* r,
+                                             bool& bad) {
   const float mass = r[1];
   if (!(fabsf(mass - 1.f) <= kMassTol)) bad = true;
   const float r1 = inv(mass), md = r[0] * r1;
   if (a.w_soft) a.w_soft[at] = (wt - md) * a.inv_kap;
   if constexpr (VJP) {
-    if (a.dW) a.dW[at] = fmaf(r[2] * r1, r[0], -r[3]) * r1 * a.dws;
+    if (!(fabsf(r[2]) + fabsf(r[3]) < INFINITY)) bad = true;
+    if (a.dW) a.dW[at] = ldexpf(fmaf(r[2] * r1, r[0], -r[3]) * r1 * a.dws, ge);
   }
 }
 
@@ -262,6 +292,8 @@ __device__ __forceinline__ double log2_split(float x) {
   const int e = (int)((as_u(x) >> 23) & 0xFFu) - 127;
   return (double)e + (double)lg2(ldexpf(x, -e));
 }
+
+__device__ __forceinline__ double pow2_d(int e) { return __longlong_as_double((long long)(e + 1023) << 52); }
 
 __device__ __forceinline__ double seg_sum_d(double v, int width) {
   for (int o = 1; o < width; o <<= 1) v += __shfl_xor(v, o);
@@ -276,7 +308,7 @@ __device__ __forceinline__ double seg_sum_d(double v, int width) {
 // one wave per workgroup, free of the others.  Against the log-domain kernel
 // with its third sweep: 64 blocks of 16 steps at S = 16 with dCodebook 106 ->
 // 24 us for the call (15 us in here, the latency of 32 dependent steps; the
-// rest launches).
+// rest launches); S = 256, 4096 blocks of 256, w_soft + logZ + dW 687 -> 378 us.
 // ---------------------------------------------------------------------------
 template <int KB, int n, bool VJP, bool DC>
 __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs a) {
@@ -287,6 +319,7 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
   constexpr int NM = VJP ? 4 : 2;
   __shared__ float2 xw[64];                  // (value, tangent) of each lane's group
   __shared__ __align__(16) float mom[BATCH ? Q * 64 * NM : 4];
+  __shared__ int gexp[64 / GS];              // (see Rows)
   const int lane = threadIdx.x;
   const int v = lane & (GS - 1);             // the lane's group
   const int seg0 = lane & ~(GS - 1);
@@ -339,6 +372,7 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
     rw.lo = clo;
     rw.hi = chi;
     rw.li = v;
+    rw.gexp = gexp;
     rw.seg0 = seg0;
     bool bad = false;
 
@@ -354,6 +388,7 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
     double far = 0.0;                        // what the exponents leave out
     {
       const int top = (L - 1) / GS * GS;
+      if constexpr (VJP) rw.scale();
       rw.load(top, rw.nw, rw.ng);
       rw.take(top, top - GS, bad);
       far += (double)rw.cf;
@@ -460,7 +495,7 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
           float wt = rw.at(rw.cw, t);
           float gt = VJP ? rw.at(rw.cg, t) : 0.f;
           float mf = rw.at(rw.cm, t);
-      lin::to_vgpr(wt, gt, mf);
+          lin::to_vgpr(wt, gt, mf);
           const float noff = rw.at(rw.cf, t) - (float)off;
           // alpha_t beta_t / Z = alpha H sc, exponents of both vectors and Z;
           // (ex - off: of alpha_t; the stored H_t carries no rescale of its own)
@@ -529,7 +564,7 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
           } else {
 #pragma unroll
             for (int c = 0; c < NM; ++c) m[c] = seg_reduce<false>(m[c], GS);
-            if (v == 0 && valid) lin::step_outputs<VJP>(a, bb * L + t, wt - mf, m, bad);
+            if (v == 0 && valid) lin::step_outputs<VJP>(a, bb * L + t, wt - mf, rw.ge(), m, bad);
           }
           lin::wave_sync();
         }
@@ -541,7 +576,7 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
         lin::sum_batch<GS, Q, NM>(mom, ln, r);
         const int t = t0 + (lv / (GS / Q));
         const float wt = __shfl(rw.cw - rw.cm, (ln & ~(GS - 1)) + t - rw.base);
-        if (t < L && valid && lv % (GS / Q) == 0) lin::step_outputs<VJP>(a, bb * L + t, wt, r, bad);
+        if (t < L && valid && lv % (GS / Q) == 0) lin::step_outputs<VJP>(a, bb * L + t, wt, rw.ge(), r, bad);
         lin::wave_sync();
       }
     }
@@ -552,8 +587,9 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
     if (v == 0 && valid) a.flags[bb] = bad ? 1 : 0;
     if constexpr (DC) {
       if (valid && !bad) {
+        const double pow2 = lin::pow2_d(rw.ge());
 #pragma unroll
-        for (int j = 0; j < K; ++j) part[j * GS + v] += (double)acc[j];
+        for (int j = 0; j < K; ++j) part[j * GS + v] = fma((double)acc[j], pow2, part[j * GS + v]);
       }
     }
   }
@@ -566,10 +602,9 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
 // values and tangents in planes of their own: a row access (K consecutive
 // groups) is then 16 bytes at a 16-byte lane stride, a column access one
 // dword per lane, both without bank conflicts.  Bound by VALU issue.  Against
-// the log-domain kernel: S = 256, 4096 blocks of 256, w_soft + logZ + dW 687 ->
-// 432 us; S = 4096, 16384 blocks with dCodebook 41.1 -> 20.3 ms; S = 16384,
-// 1800 blocks of 200, Viterbi + VJP 15.3 -> 9.9 ms.  Reducing all moments in
-// every step took 24.4 ms at S = 4096.
+// the log-domain kernel: S = 4096, 16384 blocks with dCodebook 41.1 -> 20.0 ms;
+// S = 16384, 1800 blocks of 200, Viterbi + VJP 15.3 -> 10.0 ms.  Reducing all
+// moments in every step took 24.4 ms at S = 4096.
 // ---------------------------------------------------------------------------
 template <int KB, int n, int SGT, bool VJP, bool DC>
 __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB, SGT, VJP))
@@ -604,12 +639,13 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
 
   // LDS: per block [2 copies][value, tangent][GS], each wave's moments of a
   // batch, the waves' sums of a batch and their maxima of a step (each with
-  // two parities: one barrier per step)
+  // two parities: one barrier per step); several blocks' powers of two
   constexpr int PL = VJP ? 2 : 1;            // planes
   float* const vb = lds + sub * 2 * PL * GS;
   float* const mom = lds + bpw * 2 * PL * GS + wave * Q * E * NM;
   float* const wsum = lds + bpw * 2 * PL * GS + NW * Q * E * NM;
   uint32_t* const wmax = reinterpret_cast<uint32_t*>(wsum + 2 * NW * Q * NM);
+  int* const gexp = reinterpret_cast<int*>(wsum);  // (one wave: no sums of waves)
   // largest entry over the block, from each wave's; call around the barrier
   auto max_pre = [&](float m, int par) -> uint32_t {
     const uint32_t b = lin::max_bits<W>(as_u(m));
@@ -700,6 +736,7 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
     rw.lo = clo;
     rw.hi = chi;
     rw.li = lane & (W - 1);
+    rw.gexp = gexp;
     rw.seg0 = seg0;
     bool bad = false;
     const bool first_wave = !MW || wave == 0;
@@ -720,6 +757,7 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
     int par = 0;                             // the copy being read
     {
       const int top = (L - 1) / W * W;
+      if constexpr (VJP) rw.scale();
       rw.load(top, rw.nw, rw.ng);
       rw.take(top, top - W, bad);
       far += (double)rw.cf;
@@ -994,13 +1032,13 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
 #pragma unroll
                 for (int c = 0; c < NM; ++c) r[c] += x[c];
               }
-              if (t0 + ln < L) lin::step_outputs<VJP>(a, bb * L + t0 + ln, ws, r, bad);
+              if (t0 + ln < L) lin::step_outputs<VJP>(a, bb * L + t0 + ln, ws, rw.ge(), r, bad);
             }
           }
         } else {
           const int ts = t0 + (ln & (W - 1)) / (W / Q);
           const float ws = __shfl(rw.cw - rw.cm, (ln & ~(W - 1)) + ts - rw.base);
-          if (ts < L && valid && (ln & (W - 1)) % (W / Q) == 0) lin::step_outputs<VJP>(a, bb * L + ts, ws, r, bad);
+          if (ts < L && valid && (ln & (W - 1)) % (W / Q) == 0) lin::step_outputs<VJP>(a, bb * L + ts, ws, rw.ge(), r, bad);
         }
       }
       ex -= off;
@@ -1021,13 +1059,14 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
     if (tb == 0 && valid) a.flags[bb] = bad ? 1 : 0;
     if constexpr (DC) {
       if (valid && !bad) {
+        const double pow2 = lin::pow2_d(rw.ge());
 #pragma unroll
         for (int i = 0; i < SGT; ++i)
 #pragma unroll
           for (int j = 0; j < K; ++j) {
             double* const pj = part_at(i, j);
 #pragma unroll
-            for (int u = 0; u < K; ++u) pj[u] += (double)acc[i][j][u];
+            for (int u = 0; u < K; ++u) pj[u] = fma((double)acc[i][j][u], pow2, pj[u]);
             asm volatile("" ::: "memory");
           }
       }

@@ -113,3 +113,49 @@ def test_non_finite_weights_stay_in_their_block():
     for x, y in zip(a[:3], b[:3]):
         assert torch.equal(x[keep], y[keep])
     assert not torch.isfinite(b[0][4]).all()
+
+
+def call(w, c, g, n, k, T, dc, nbytes=None):
+    """The fused call in a workspace filled with 0xFF; with its outputs the
+    flags of the blocks, which the linear-domain kernels leave behind the
+    scaled codebook: 1 for a block they marked (another value there: another
+    kernel family ran)."""
+    B, L = w.shape
+    if nbytes is None:
+        nbytes = P.bcjr_workspace_bytes(B, L, n, k, P.OP_FWD_VJP)
+    work = torch.full((nbytes,), 255, dtype=torch.uint8, device="cuda:0")
+    out = P.bcjr_soft_codeword_fwd_vjp(dev(w), dev(c), n, k, T, dev(g), want_dCodebook=dc, workspace=work)
+    torch.cuda.synchronize()
+    at = (4 * len(c) + 255) // 256 * 256
+    return [None if x is None else x.cpu().numpy() for x in out], work[at:at + 4 * B].view(torch.int32).cpu().numpy()
+
+
+@pytest.mark.parametrize("n,k", [(2, 1), (4, 2), (8, 2), (8, 1), (9, 3), (10, 3), (11, 2), (12, 2), (15, 2)])
+@pytest.mark.parametrize("T", [0.25, 1.0])
+def test_any_gradient_scale(n, k, T):
+    """The gradients are linear in g and a power of two is taken out of every
+    block's g exactly: each block's g times its own 2^x yields the same bits
+    of dW times 2^x, and the whole g times 2^x those of dCodebook (entries in
+    the subnormal range carry one rounding there).  No block is marked, so
+    all of it is the linear-domain kernels' own."""
+    r = np.random.default_rng(13 * n + k)
+    c = r.standard_normal(1 << n).astype(np.float32)
+    B, L = 320 if n < 8 else 12, 70
+    w = r.standard_normal((B, L)).astype(np.float32)
+    g = r.standard_normal((B, L)).astype(np.float32)
+
+    def run(gr, dc):
+        out, flags = call(w, c, gr, n, k, T, dc)
+        assert not flags.any()
+        return out[2:]
+
+    print(f"[lin-small] gradient scales n={n} k={k} T={T}", file=sys.__stderr__, flush=True)
+    dW = run(g, False)[0]
+    x = r.choice([-90, -50, -20, 0, 16, 24, 36, 60, 100], (B, 1))
+    got = run(np.ldexp(g, x), False)[0]
+    assert (np.abs(got - np.ldexp(dW, x)) <= 2.0 ** (np.maximum(x, 0) - 149)).all()
+    dW, dC = run(g, True)
+    for e in (-60, -30, 20, 36, 100):
+        a, b = run(np.ldexp(g, e), True)
+        tol = 2.0 ** (max(e, 0) - 149)
+        assert (np.abs(a - np.ldexp(dW, e)) <= tol).all() and (np.abs(b - np.ldexp(dC, e)) <= tol).all()
