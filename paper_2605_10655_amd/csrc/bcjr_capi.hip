@@ -715,10 +715,14 @@ int run_lin_small(const float* w, int64_t B, int64_t L, const float* codebook, i
   // memory, no more slots than there are partials
   const FbLayout lay = fb_layout(L, n, k, vjp, dc);
   const int64_t rep_wg = f.bpw * (int64_t)(lay.hist + lay.histGA + lay.small);
-  const int64_t region = (int64_t)ws_bytes - front - (int64_t)kAlign;
-  if (region < rep_wg) return BCJR_ERR_WORKSPACE;
-  const int64_t fit = std::min<int64_t>((region - (int64_t)kAlign) / (hist + exb + dcb),
-                                        dcb ? (region - rep_wg) / dcb : B);
+  const int64_t avail = (int64_t)ws_bytes - front;
+  if (avail < rep_wg) return BCJR_ERR_WORKSPACE;
+  // slots that fit, those of a wave's lanes beyond B included: the queried
+  // workspace holds as many as the log-domain kernel's workgroups, exactly
+  auto up = [](int64_t x) { return (int64_t)align_up((size_t)x); };
+  int64_t fit = avail / (hist + exb + dcb);
+  if (dc) fit = std::min(fit, (avail - rep_wg) / dcb);
+  while (fit > 0 && up(fit * dcb) + std::max(rep_wg, up(fit * exb) + fit * hist) > avail) --fit;
   Family fl;
   fl.nt = sh.nt;
   fl.bpw = sh.bpw;

@@ -159,3 +159,30 @@ def test_any_gradient_scale(n, k, T):
         a, b = run(np.ldexp(g, e), True)
         tol = 2.0 ** (max(e, 0) - 149)
         assert (np.abs(a - np.ldexp(dW, e)) <= tol).all() and (np.abs(b - np.ldexp(dC, e)) <= tol).all()
+
+
+@pytest.mark.parametrize("n,k", SHAPES)
+def test_small_batches_run_the_same_kernels(n, k):
+    """Batches that leave a wave's last blocks empty, down to one block, run the
+    linear-domain kernels as large ones do: their flags say so, and every
+    output has the bits that it has inside a batch of 130."""
+    r = np.random.default_rng(17 * n + k)
+    c = r.standard_normal(1 << n).astype(np.float32)
+    w = r.standard_normal((130, 21)).astype(np.float32)
+    g = r.standard_normal((130, 21)).astype(np.float32)
+    at = (4 << n) + 255 & -256
+
+    def soft(x):
+        work = torch.full((P.bcjr_workspace_bytes(len(x), 21, n, k, P.OP_FWD),), 255, dtype=torch.uint8, device="cuda:0")
+        out = P.bcjr_soft_codeword(dev(x), dev(c), n, k, 0.25, workspace=work)
+        return [y.cpu().numpy() for y in out], work[at:at + 4 * len(x)].view(torch.int32).cpu().numpy()
+
+    runs = [soft] + [lambda x, dc=dc: call(x, c, g[:len(x)], n, k, 0.25, dc) for dc in (False, True)]
+    for i, run in enumerate(runs):
+        big, marks = run(w)
+        assert set(marks) <= {0, 1}, "the batch of 130"
+        for B in (1, 3, 31):
+            out, flags = run(w[:B])
+            assert np.array_equal(flags, marks[:B]), f"call {i}, B = {B}"
+            for a, b in zip(out[:3], big[:3]):
+                np.testing.assert_array_equal(a, b[:B])
