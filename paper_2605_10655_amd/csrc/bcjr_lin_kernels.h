@@ -105,10 +105,13 @@ constexpr int kTopExp = 90;
 constexpr float kTop = 0x1p90f;
 constexpr uint32_t kFloorBits = 0x2D800000u;  // 2^-36
 constexpr uint32_t kCeilBits = 0x79800000u;   // 2^116
-// alpha H of the step's states in the stored units is 2^-es / Z's mantissa: with
-// es above this they lie 200 log2 units below the vectors' largest entries,
-// and H times the scale could leave the range elsewhere
-constexpr int kScaleMax = 20;
+// With Z's mantissa in [1, 2), alpha H of a step's states sums to 2^-es in the
+// stored units.  A path with an exponential below 2^-126 is lost, which may weigh
+// up to 2^62 there (the vectors' entries reach 2^91 and, unscaled, 2^94), and
+// both sweeps lose the same ones, so that the mass does not show it: against 64
+// bits (256 steps, T = 0.0225 to 0.1) no block of 2000 is over 2e-5 off with all
+// es below -70; from there up 4 % are, by up to the codebook's range.
+constexpr int kScaleMax = -75;
 // log2 units of a weight's distance outside the codebook (its exponents round
 // at 6e-8 of them); beyond, the block is marked
 constexpr float kFarMax = 4096.f;
@@ -287,11 +290,8 @@ __device__ __forceinline__ void step_outputs(const LinArgs& a, int64_t at, float
   }
 }
 
-// log2 of a normal x, its exponent kept apart from the rounded logarithm
-__device__ __forceinline__ double log2_split(float x) {
-  const int e = (int)((as_u(x) >> 23) & 0xFFu) - 127;
-  return (double)e + (double)lg2(ldexpf(x, -e));
-}
+// e with x = m 2^e, 1 <= m < 2, for a positive normal x
+__device__ __forceinline__ int exp_bits(float x) { return (int)((as_u(x) >> 23) & 0xFFu) - 127; }
 
 __device__ __forceinline__ double pow2_d(int e) { return __longlong_as_double((long long)(e + 1023) << 52); }
 
@@ -453,12 +453,14 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
       ls = seg_reduce<false>(ls, GS);
       if constexpr (VJP) ly = seg_reduce<false>(ly, GS);
       if (!(ls > 0.f && ls < INFINITY)) bad = true;
+      const int ez = lin::exp_bits(ls);
+      ls = ldexpf(ls, -ez);
       rz = lin::inv(ls);
-      exz = ex - off;
-      xbar = ly * rz;
+      exz = ex - off - ez;
+      xbar = ldexpf(ly, -ez) * rz;
       far = lin::seg_sum_d(far, GS);
       if (v == 0 && valid && a.logZ)
-        a.logZ[bb] = (float)((lin::log2_split(ls) - (double)exz - far) * 0.69314718055994530942);
+        a.logZ[bb] = (float)(((double)lg2(ls) - (double)exz - far) * 0.69314718055994530942);
     }
 
     // ------------------------------------------------------------- forward
@@ -856,12 +858,14 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
       lin::block_sync<MW>();
       red_post<2, 0u>(sv, rc);
       if (!(sv[0] > 0.f && sv[0] < INFINITY)) bad = true;
+      const int ez = lin::exp_bits(sv[0]);
+      sv[0] = ldexpf(sv[0], -ez);
       rz = lin::inv(sv[0]);
-      exz = ex - off;
-      xbar = sv[1] * rz;
+      exz = ex - off - ez;
+      xbar = ldexpf(sv[1], -ez) * rz;
       far = lin::seg_sum_d(far, W);
       if (tb == 0 && valid && a.logZ)
-        a.logZ[bb] = (float)((lin::log2_split(sv[0]) - (double)exz - far) * 0.69314718055994530942);
+        a.logZ[bb] = (float)(((double)lg2(sv[0]) - (double)exz - far) * 0.69314718055994530942);
       lin::block_sync<MW>();
     }
 

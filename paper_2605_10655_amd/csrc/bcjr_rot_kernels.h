@@ -416,6 +416,14 @@ constexpr float top(bool dc) { return dc ? 0x1p90f : 0x1p50f; }
 // below T = 0.04, where the double-float pass does better; with dCodebook,
 // whose moments are about the edge of the range, 4096.
 
+// A path is lost where an exponential is below 2^-126, in both sweeps, so that
+// the mass does not show it.  It may weigh 2^-24 in the units of alpha H there
+// (2^62 with dCodebook); blocks whose states' alpha H sum to less than
+// kMassMin (2^-kScaleMax) at some step are marked.  (2^-12 would mark blocks of
+// N(0, 1) weights at T = 0.021, for 10 % of that call.)
+constexpr float kMassMin = 0x1p-18f;
+constexpr int kScaleMax = -75;
+
 // e with x = m 2^e, 1 <= m < 2, for a positive normal x (-127 for zero or a
 // denormal, 128 for inf or NaN)
 __device__ __forceinline__ int exp_of(float x) { return (int)((__float_as_uint(x) >> 23) & 0xFFu) - 127; }
@@ -439,7 +447,8 @@ __device__ __forceinline__ int exp_of(float x) { return (int)((__float_as_uint(x
 // A block whose vectors leave that range -- a step whose largest entry
 // falls below 2^-30 (a single-step decay of 80 log2 units, which the
 // posterior states would not survive), the forward's per-step mass
-// sum_s alpha_t beta_t departing from Z by more than 2e-4 log2 units, or a
+// sum_s alpha_t beta_t departing from Z by more than 2e-4 log2 units, alpha H
+// of a step so small that a better path may have been lost (kMassMin), or a
 // step's tangent moments not finite -- is marked in a.flags and recomputed by
 // a second launch of the log-domain (or, at field scales above 18, the
 // double-float) kernel in repair mode.
@@ -640,9 +649,10 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
         if (!(sv[0] > 0.f && sv[0] < INFINITY)) bad = true;
         lz2 = lg2(sv[0]) - (float)(ex - off);
         xbar = sv[1] / sv[0];
-        if constexpr (DC) {
-          rz = 1.f / sv[0];
-          exz = ex - off;
+        if constexpr (DC) {  // (Z's exponent apart: see kScaleMax)
+          const int ez = rot::exp_of(sv[0]);
+          rz = 1.f / ldexpf(sv[0], -ez);
+          exz = ex - off - ez;
         }
         if (threadIdx.x == 0 && a.logZ) a.logZ[bb] = (float)(((double)lz2 - (double)far) * 0.69314718055994530942);
         __syncthreads();
@@ -763,9 +773,7 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
       int es = 0;
       if constexpr (DC) {
         es = exz - (ex - off) - (int)eHt;
-        // (the states' alpha H 200 log2 units below the largest entries' product:
-        // H times the scale could leave the range elsewhere)
-        if (es > 20) bad = true;
+        if (es > rot::kScaleMax) bad = true;
         gsc = gt * rz;
         dsc = dws * rz;
       }
@@ -897,6 +905,7 @@ __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
       } else {
         const float lzt = lg2(rv[2]) - (float)(ex - off) - eHt;
         if (!(fabsf(lzt - lz2) <= 2e-4f)) bad = true;
+        if (!(rv[2] >= rot::kMassMin)) bad = true;
       }
       if (!(rv[0] >= rot::floor_of(DC) && rv[0] <= rot::ceil_of(DC))) bad = true;
       ex -= off;

@@ -272,3 +272,23 @@ def test_linear_kernel_takes_any_gradient_scale(L, T, want_dc):
     assert (np.abs(got - want) <= 2.0 ** (np.maximum(rows, 0) - 149)).all()
     g[1] = 0.0
     assert not run(g)[0][1].any()
+
+
+@pytest.mark.parametrize("want_dc", [False, True])
+def test_a_path_that_both_sweeps_lose_marks_its_block(want_dc):
+    """As below 65536 states (tests/test_gpu_lin_small.py): the second best
+    path is the best that fp32 exponentials keep, and both sweeps agree on it."""
+    from test_gpu_lin_small import lost_path
+    w, c, g = lost_path(N, KB, 77)
+    ref = O.soft_codeword_vjp(w, c, N, KB, 0.25, g)
+    assert ref[0][1, 0] > 8.0
+    work = torch.full((P.bcjr_workspace_bytes(5, 12, N, KB, P.OP_FWD_VJP),), 255, dtype=torch.uint8, device="cuda:0")
+    out = P.bcjr_soft_codeword_fwd_vjp(dev(w), dev(c), N, KB, 0.25, dev(g), want_dCodebook=want_dc, workspace=work)
+    soft = P.bcjr_soft_codeword(dev(w), dev(c), N, KB, 0.25)
+    torch.cuda.synchronize()
+    assert work[4 << N:][:20].view(torch.int32).tolist() == [0, 1, 0, 1, 0]
+    for x in (out[0], soft[0]):
+        assert np.abs(x.cpu().numpy() - ref[0]).max() <= TOL_WS
+    tol = 2.0 ** -22 * np.abs(g).max() * 9.0 ** 2 / 0.25  # (as there)
+    for a, b in zip(out[2:4], ref[2:4]):
+        assert a is None or np.abs(a.cpu().numpy() - b).max() <= tol + TOL_GRAD * np.abs(b).max()

@@ -186,3 +186,42 @@ def test_small_batches_run_the_same_kernels(n, k):
             assert np.array_equal(flags, marks[:B]), f"call {i}, B = {B}"
             for a, b in zip(out[:3], big[:3]):
                 np.testing.assert_array_equal(a, b[:B])
+
+
+def lost_path(n, k, seed):
+    """Blocks of 12 weights at T = 0.25 (2.885 log2 units per unit of squared
+    distance) on a codebook that tells only whether a state's last two digits
+    are 0.  Weight 0 lies on the codewords of (x, 0) and over 126 units from
+    all others of its kind, weights 1 and 2 on those of (x, y) and 83 units from
+    (0, 0): the best path begins with a step of 137 units, whose exponential is
+    0 in fp32, the best without it has two steps of 83."""
+    r = np.random.default_rng(seed)
+    s = np.arange(1 << n)
+    p, q = (s >> k) % (1 << k) > 0, s % (1 << k) > 0
+    c = np.select([~p & ~q, ~p & q, p & ~q], [0.0, 8.9, 2.0], -5.364)
+    w = np.zeros((5, 12))
+    w[[1, 3], 0], w[[1, 3], 1:3] = 2.0, -5.364
+    w[3, 8], w[3, 9:11] = 2.0, -5.364      # and the same inside the block
+    c, w = c + 0.01 * r.standard_normal(1 << n), w + 0.01 * r.standard_normal(w.shape)
+    return w.astype(np.float32), c.astype(np.float32), r.standard_normal(w.shape).astype(np.float32)
+
+
+@pytest.mark.parametrize("n,k", SHAPES)
+def test_a_path_that_both_sweeps_lose_marks_its_block(n, k):
+    """Both sweeps lose the best path alike and their masses agree on the
+    second best: only the size of alpha H shows it.  (The codewords of a kind
+    are nearly alike, so that the gradients are small: their bound is the tangents'
+    rounding, 2^-22 |g D| of a weight at distance D, times D / T.)"""
+    w, c, g = lost_path(n, k, 23 * n + k)
+    ref = O.soft_codeword_vjp(w, c, n, k, 0.25, g)
+    assert ref[0][1, 0] > 8.0  # (the second best starts at 2)
+    tol = 2.0 ** -22 * np.abs(g).max() * 9.0 ** 2 / 0.25
+    soft = P.bcjr_soft_codeword(dev(w), dev(c), n, k, 0.25)
+    assert np.abs(soft[0].cpu().numpy() - ref[0]).max() <= 2e-5
+    for dc in (False, True):
+        out, flags = call(w, c, g, n, k, 0.25, dc)
+        assert flags.tolist() == [0, 1, 0, 1, 0]
+        assert np.abs(out[0] - ref[0]).max() <= 2e-5
+        assert np.abs(out[1] - ref[1]).max() <= 1e-4 * np.abs(ref[1]).max()
+        for a, b in zip(out[2:], ref[2:]):
+            assert a is None or np.abs(a - b).max() <= tol + 1e-4 * np.abs(b).max()
