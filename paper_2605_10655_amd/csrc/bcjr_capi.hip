@@ -208,24 +208,29 @@ using VitFn = void (*)(VitArgs);
 // the others are compiled per state-bit count so that every LDS and codebook
 // offset folds into an immediate.
 template <int KB, int NB, int SGM, int NT>
-FbFn fb_variant(bool vjp, bool dc) {
-  if (!vjp) return fb_kernel<KB, NB, SGM, NT, false, false>;
-  if (!dc) return fb_kernel<KB, NB, SGM, NT, true, false>;
-  return fb_kernel<KB, NB, SGM, NT, true, true>;
+FbFn fb_variant(bool vjp, bool dc, bool rep) {
+  if (rep) {
+    if (!vjp) return fb_kernel<KB, NB, SGM, NT, false, false, true>;
+    if (!dc) return fb_kernel<KB, NB, SGM, NT, true, false, true>;
+    return fb_kernel<KB, NB, SGM, NT, true, true, true>;
+  }
+  if (!vjp) return fb_kernel<KB, NB, SGM, NT, false, false, false>;
+  if (!dc) return fb_kernel<KB, NB, SGM, NT, true, false, false>;
+  return fb_kernel<KB, NB, SGM, NT, true, true, false>;
 }
 
 template <int KB>
-FbFn fb_pick_kb(int n, const Family& f, bool vjp, bool dc) {
-  if (f.sgmax == 1) return fb_variant<KB, 0, 1, 256>(vjp, dc);
+FbFn fb_pick_kb(int n, const Family& f, bool vjp, bool dc, bool rep) {
+  if (f.sgmax == 1) return fb_variant<KB, 0, 1, 256>(vjp, dc, rep);
   if constexpr (KB < 3) {
     // nsg = 2^(n - 2KB): 512, 1024, 2048 -> 256 threads; 4096 -> 512 (fb_family)
     constexpr int n512 = 2 * KB + 9;
     if (f.nt == 256) {
-      if (n == n512) return fb_variant<KB, n512, 2, 256>(vjp, dc);
-      if (n == n512 + 1) return fb_variant<KB, n512 + 1, 4, 256>(vjp, dc);
-      if (n == n512 + 2) return fb_variant<KB, n512 + 2, 8, 256>(vjp, dc);
+      if (n == n512) return fb_variant<KB, n512, 2, 256>(vjp, dc, rep);
+      if (n == n512 + 1) return fb_variant<KB, n512 + 1, 4, 256>(vjp, dc, rep);
+      if (n == n512 + 2) return fb_variant<KB, n512 + 2, 8, 256>(vjp, dc, rep);
     }
-    if (n == n512 + 3 && f.nt == 512) return fb_variant<KB, n512 + 3, 8, 512>(vjp, dc);
+    if (n == n512 + 3 && f.nt == 512) return fb_variant<KB, n512 + 3, 8, 512>(vjp, dc, rep);
   }
   return nullptr;
 }
@@ -255,11 +260,11 @@ FbFn hp_pick(int n, int k, const Family& f, bool dc) {
   }
 }
 
-FbFn fb_pick(int n, int k, const Family& f, bool vjp, bool dc) {
+FbFn fb_pick(int n, int k, const Family& f, bool vjp, bool dc, bool rep) {
   switch (k) {
-    case 1: return fb_pick_kb<1>(n, f, vjp, dc);
-    case 2: return fb_pick_kb<2>(n, f, vjp, dc);
-    case 3: return fb_pick_kb<3>(n, f, vjp, dc);
+    case 1: return fb_pick_kb<1>(n, f, vjp, dc, rep);
+    case 2: return fb_pick_kb<2>(n, f, vjp, dc, rep);
+    case 3: return fb_pick_kb<3>(n, f, vjp, dc, rep);
     default: return nullptr;
   }
 }
@@ -286,7 +291,6 @@ VitFn vit_pick(int n, int k, const Family& f) {
   }
 }
 
-// the fp32 min-sum decode of the centring reference, same families
 // the MIN form of the shapes of 4096 super-groups
 VitFn vit_min_pick(int n, int k) {
   if (k == 2 && n == 16) return viterbi_kernel<2, 16, 4, 1024, true>;
@@ -294,6 +298,7 @@ VitFn vit_min_pick(int n, int k) {
   return nullptr;
 }
 
+// the fp32 min-sum decode of the centring reference, same families
 template <int KB>
 VitFn vit_ref_pick_kb(int n, const Family& f) {
   if (f.sgmax == 1) return viterbi_ref_kernel<KB, 0, 1, 256>;
@@ -704,7 +709,7 @@ int run_lin_small(const float* w, int64_t B, int64_t L, const float* codebook, i
   const bool dc = vjp && dCodebook != nullptr;
   const LinShape sh = lin_shape(n, k, vjp, dc);
   const Family f = fb_family(n, k, dc);
-  FbFn rep = fb_pick(n, k, f, vjp, dc);
+  FbFn rep = fb_pick(n, k, f, vjp, dc, true);
   if (!sh.fn || !rep) return BCJR_ERR_WORKSPACE;
   const int64_t front = (int64_t)(cs_bytes(n) + flag_bytes(B));
   const int64_t S = (int64_t)1 << n;
@@ -815,7 +820,7 @@ int run_fb_lin(const float* w, int64_t B, int64_t L, const float* codebook, int 
   if (herr) return BCJR_ERR_HIP;
   if (grid < 1) return BCJR_ERR_WORKSPACE;
   const size_t lds_rep = fb_lds_bytes(f, n, k);
-  FbFn rep_fn = vjp && !dc ? nullptr : fb_pick(n, k, f, vjp, dc);
+  FbFn rep_fn = vjp && !dc ? nullptr : fb_pick(n, k, f, vjp, dc, true);
   if ((!vjp || dc) && !rep_fn) return BCJR_ERR_UNSUPPORTED;
   const void* rep_kern = vjp && !dc ? fb_rot_kernel() : (const void*)rep_fn;
   if (!hp && hipFuncSetAttribute(rep_kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_rep) !=
@@ -903,7 +908,7 @@ int run_fb(const float* w, int64_t B, int64_t L, const float* codebook, int n, i
   const bool dc = vjp && dCodebook != nullptr;
   const Family f = fb_family(n, k, dc);
   const FbLayout lay = fb_layout(L, n, k, vjp, dc);
-  FbFn fn = fb_pick(n, k, f, vjp, dc);
+  FbFn fn = fb_pick(n, k, f, vjp, dc, false);
   if (!fn) return BCJR_ERR_UNSUPPORTED;
   const size_t lds = fb_lds_bytes(f, n, k);
   int herr = 0;

@@ -32,8 +32,9 @@
 //   workgroup above 64 lanes, one or several per one-wave workgroup below.
 //
 // A block whose vectors leave the number range -- a step's largest entry
-// below a floor, the forward mass sum_s alpha_t beta_t / Z away from 1, a
-// weight far outside the codebook, moments that are not finite -- is marked in
+// below a floor, the forward mass sum_s alpha_t beta_t / Z away from 1, alpha H
+// of a step so small that a better path may have been lost (kScaleMax), a weight
+// far outside the codebook, moments that are not finite -- is marked in
 // a.flags and recomputed by a second launch of the log-domain kernels.  The
 // tangents' range does not depend on the gradient's: a power of two per block
 // is taken out of g when its rows are read and put back at dW and dCodebook
