@@ -688,15 +688,27 @@ int reduce_dc(const double* part, int64_t slots, int64_t S, float* out, hipStrea
   return hipGetLastError() == hipSuccess ? BCJR_OK : BCJR_ERR_HIP;
 }
 
-// The linear-domain kernels below 65536 states (bcjr_lin_kernels.h): the soft
-// codeword to the field scale of the 65536-state one, the VJP, with or
-// without dCodebook, where fp32 log vectors serve it (T >= 0.04): S = 4096 with
-// dCodebook 20.3 ms against 41.1 in the log domain (16384 blocks, T = 0.1);
-// below, dCodebook in fp32 sums (tried at 65536 states) is 1.3e-6 to 2.7e-6 off where the double-float
-// kernel is 4e-7.
-bool lin_small_ok(int n, int k, float T, bool vjp) {
+// Where the linear-domain kernels below 65536 states (bcjr_lin_kernels.h) serve.
+// The VJP where fp32 vectors do (T >= 0.04; below, dCodebook in fp32 sums, tried
+// at 65536 states, is 1.3e-6 to 2.7e-6 off where the double-float kernel is
+// 4e-7): S = 4096 with dCodebook 20.3 ms against 41.1 in the log domain (16384
+// blocks, T = 0.1).  A marked block costs the log-domain kernel's whole latency
+// again, so the line lies where blocks of N(0, 1) weights are hardly ever
+// marked (2000 blocks of 200, us, log domain -> here):
+//  * k = 1, whose two predecessors leave the weights far from the codewords: at
+//    T = 0.05 4 to 24 % of the blocks are marked (S = 256, soft 405 -> 752, S = 2048
+//    with dW 1629 -> 2586), at T = 0.1 less than one in a thousand (S = 32 287 -> 107).
+//    Above 64 groups without dCodebook the gain is 0 to 17 % even unmarked, and at
+//    T = 0.1 heavy tails cost 75 %: from T = 0.2.  (With it, S = 256, T = 0.07: 749
+//    -> 1052; T = 0.1: 466.)
+//  * the soft codeword at T < 0.04: S = 128 at T = 0.0225 407 -> 945, S = 512 444 ->
+//    640; from 4096 states no slower at T = 0.0225 (1384 -> 1350; S = 16384, 800
+//    blocks 1985 -> 1653, but 2004 -> 2415 at T = 0.021).
+bool lin_small_ok(int n, int k, float T, bool vjp, bool dc) {
   if (!supported(n, k) || (n == 16 && k == 2)) return false;
-  return vjp ? !use_high_precision(T) : 1.4426950408889634074 / (2.0 * (double)T) <= kLinearK2;
+  if (k == 1) return T >= (dc || n < 8 ? 0.1f : 0.2f);
+  if (vjp || n < 12) return !use_high_precision(T);
+  return T >= 0.0225f;
 }
 
 // [scaled codebook][block flags][dCodebook partials][exponents][histories].
@@ -892,7 +904,7 @@ int run_fb(const float* w, int64_t B, int64_t L, const float* codebook, int n, i
     // (a workspace too small for the dCodebook form: the log-domain kernel)
     if (st != BCJR_ERR_WORKSPACE || !dCodebook) return st;
   }
-  if (lin_small_ok(n, k, T, vjp)) {
+  if (lin_small_ok(n, k, T, vjp, dCodebook != nullptr)) {
     const int st = run_lin_small(w, B, L, codebook, n, k, T, g, w_soft, logZ, dW, dCodebook, workspace,
                                  ws_bytes, stream, vjp);
     if (st != BCJR_ERR_WORKSPACE) return st;  // (a workspace too small for it: the log-domain kernel)

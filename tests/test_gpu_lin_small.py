@@ -225,3 +225,29 @@ def test_a_path_that_both_sweeps_lose_marks_its_block(n, k):
         assert np.abs(out[1] - ref[1]).max() <= 1e-4 * np.abs(ref[1]).max()
         for a, b in zip(out[2:], ref[2:]):
             assert a is None or np.abs(a - b).max() <= tol + 1e-4 * np.abs(b).max()
+
+
+@pytest.mark.parametrize("n,k,T,served", [
+    (5, 1, 0.09, ""), (5, 1, 0.11, "soft dw dc"), (8, 1, 0.11, "dc"), (8, 1, 0.21, "soft dw dc"),
+    (6, 2, 0.039, ""), (6, 2, 0.041, "soft dw dc"), (12, 2, 0.022, ""), (12, 2, 0.023, "soft"),
+    (11, 3, 0.039, ""), (12, 3, 0.023, "soft")])
+def test_temperatures_that_the_linear_kernels_serve(n, k, T, served):
+    """On each side of the lines of the dispatch (where ordinary weights begin to
+    leave the kernels' number range), each form against the oracle."""
+    r = np.random.default_rng(n + k)
+    c = r.standard_normal(1 << n).astype(np.float32)
+    w = r.standard_normal((3, 20)).astype(np.float32)
+    g = r.standard_normal((3, 20)).astype(np.float32)
+    ref = O.soft_codeword_vjp(w, c, n, k, float(np.float32(T)), g)
+    at = (4 << n) + 255 & -256
+    for form in ("soft", "dw", "dc"):
+        if form == "soft":
+            work = torch.full((P.bcjr_workspace_bytes(3, 20, n, k, P.OP_FWD),), 255, dtype=torch.uint8, device="cuda:0")
+            out = [x.cpu().numpy() for x in P.bcjr_soft_codeword(dev(w), dev(c), n, k, T, workspace=work)]
+            flags = work[at:at + 12].view(torch.int32).cpu().numpy()
+        else:
+            out, flags = call(w, c, g, n, k, T, form == "dc")
+        assert (set(flags) <= {0, 1}) == (form in served.split()), form
+        assert np.abs(out[0] - ref[0]).max() <= 2e-5
+        for a, b in zip(out[2:], ref[2:]):
+            assert a is None or grad_err(a, b) <= 1e-4
