@@ -48,14 +48,12 @@ def grad_err(gpu, ref):
     return float((np.abs(gpu.astype(np.float64) - ref) / np.where(scale > 0, scale, 1.0)).max())
 
 
-def mixed_batch(L, seed, far=40.0):
+def mixed_batch(L, seed):
     """Six blocks: 0, 1, 5 N(0, 1); 2 with four weights at +-6 (single-step
     decays of ~40 log2 units at T = 0.05); 3 with every weight at 40 (every
-    exponential underflows: marked and recomputed; `far`, 8 in the
-    dCodebook tests, is still marked at every temperature tested, and keeps
-    (w - c)(X - E X) / T within what the fp32 log-domain repair resolves:
-    at 40 that product amplifies the tangents' rounding past the dCodebook
-    tolerance, for the log-domain kernels alike); 4 N(0, 1) except one
+    exponential underflows: marked and recomputed; no dCodebook is asked of
+    these, whose (w - c)(X - E X) / T amplifies the tangents' rounding past the
+    dCodebook tolerance, for the log-domain kernels alike); 4 N(0, 1) except one
     weight at 15 mid-block (a single-step decay past the guard at every
     temperature here: marked and recomputed).  Weights further out than
     ~20 from the codebook's range put the local field at thousands of log2
@@ -67,7 +65,7 @@ def mixed_batch(L, seed, far=40.0):
         w[2, [0, L // 3, L // 2, L - 1]] = [6.0, -6.0, 6.0, -6.0]
     else:
         w[2, 0] = 6.0
-    w[3, :] = far
+    w[3, :] = 40.0
     w[4, L // 2] = 15.0
     g = r.standard_normal((6, L)).astype(np.float32)
     return w, g
@@ -292,3 +290,65 @@ def test_a_path_that_both_sweeps_lose_marks_its_block(want_dc):
     tol = 2.0 ** -22 * np.abs(g).max() * 9.0 ** 2 / 0.25  # (as there)
     for a, b in zip(out[2:4], ref[2:4]):
         assert a is None or np.abs(a.cpu().numpy() - b).max() <= tol + TOL_GRAD * np.abs(b).max()
+
+
+@pytest.mark.parametrize("T", [0.05, 0.1, 1.0])
+@pytest.mark.parametrize("L", [12, 100])
+def test_dcodebook_with_weights_outside_the_codebook(L, T):
+    """The dCodebook form takes single weights far outside the codebook's range
+    about its edge: no block is marked."""
+    c = WL.codebook(4)
+    r = np.random.Generator(np.random.PCG64(5000 + L))
+    w = r.standard_normal((4, L)).astype(np.float32)
+    w[1, 5], w[2, L // 2], w[3, 4] = 8.0, 15.0, -10.0
+    g = r.standard_normal((4, L)).astype(np.float32)
+    work = torch.full((P.bcjr_workspace_bytes(4, L, N, KB, P.OP_FWD_VJP),), 255, dtype=torch.uint8, device="cuda:0")
+    out = P.bcjr_soft_codeword_fwd_vjp(dev(w), dev(c), N, KB, T, dev(g), workspace=work)
+    torch.cuda.synchronize()
+    assert work[4 << N:][:16].view(torch.int32).tolist() == [0, 0, 0, 0]
+    ref = O.soft_codeword_vjp(w, c, N, KB, float(np.float32(T)), g)
+    out = [x.cpu().numpy() for x in out]
+    e = [float(np.abs(out[0] - ref[0]).max()), float(np.abs(out[1] / ref[1] - 1).max()), grad_err(out[2], ref[2]),
+         grad_err(out[3], ref[3])]
+    print(f"dCodebook, far weights: L={L} T={T} " + " ".join("%.1e" % x for x in e), flush=True)
+    assert e[0] <= TOL_WS and e[1] <= TOL_LOGZ and e[2] <= TOL_GRAD and e[3] <= TOL_GRAD
+
+
+def test_dcodebook_repair_pass():
+    """Marked blocks among others in the dCodebook form, in workspaces of ever
+    fewer slots: as below 65536 states."""
+    from test_gpu_lin_small import clusters, repair_bounds
+    T, marked, B, L = 0.25, [0, 3, 4], 6, 20
+    w, c, g = clusters(N, KB, B, L, marked)
+    ref = O.soft_codeword_vjp(w, c, N, KB, T, g)
+    rel, tol = repair_bounds(w, c, marked, T)
+    full = P.bcjr_workspace_bytes(B, L, N, KB, P.OP_FWD_VJP)
+    first, runs = None, 0
+    for part in (1.0, 0.75, 0.5, 0.35, 0.25, 0.2):
+        work = torch.full((int(full * part),), 255, dtype=torch.uint8, device="cuda:0")
+        try:
+            out = P.bcjr_soft_codeword_fwd_vjp(dev(w), dev(c), N, KB, T, dev(g), workspace=work)
+        except P.BcjrError as e:
+            assert e.status == -3
+            continue
+        torch.cuda.synchronize()
+        flags = work[4 << N:][:4 * B].view(torch.int32).tolist()
+        if not set(flags) <= {0, 1}:
+            continue  # (the log-domain kernel, which needs less)
+        runs += 1
+        assert [b for b in range(B) if flags[b]] == marked
+        out = [x.cpu().numpy() for x in out]
+        if first is None:
+            first = out
+            e = [float(np.abs(out[0] - ref[0]).max()), float(np.abs(out[1] / ref[1] - 1).max()),
+                 grad_err(out[2], ref[2]), grad_err(out[3], ref[3])]
+            print("dCodebook repair: " + " ".join("%.1e" % x for x in e) + f" rel {rel:.1e}", flush=True)
+            assert e[0] <= TOL_WS + tol and e[1] <= TOL_LOGZ
+            assert e[2] <= TOL_GRAD + 2 * rel and e[3] <= TOL_GRAD + 30 * rel
+            rest = [1, 2, 5]
+            assert np.abs(out[0][rest] - ref[0][rest]).max() <= TOL_WS
+        for a, b in zip(out[:3], first[:3]):
+            np.testing.assert_array_equal(a, b)
+        np.testing.assert_allclose(out[3], first[3], rtol=2.0 ** -22, atol=2.0 ** -22 * np.abs(first[3]).max())
+    print(f"dCodebook repair: {runs} workspace sizes ran", flush=True)
+    assert runs >= 2

@@ -251,3 +251,72 @@ def test_temperatures_that_the_linear_kernels_serve(n, k, T, served):
         assert np.abs(out[0] - ref[0]).max() <= 2e-5
         for a, b in zip(out[2:], ref[2:]):
             assert a is None or grad_err(a, b) <= 1e-4
+
+
+def clusters(n, k, B, L, marked):
+    """Codewords about +-7.5 and weights on them; in the blocks `marked` the
+    weights lie about 0, inside the codebook's range but 160 log2 units (at
+    T = 0.25) from every codeword, below the floor of the vectors."""
+    r = np.random.default_rng(31 * n + k)
+    c = r.standard_normal(1 << n) + 7.5 * r.choice([-1.0, 1.0], 1 << n)
+    c[:2] = -7.5, 7.5
+    w = r.standard_normal((B, L)) + 7.5 * r.choice([-1.0, 1.0], (B, L))
+    w[marked] = 0.3 * r.standard_normal((len(marked), L))
+    return w.astype(np.float32), c.astype(np.float32), r.standard_normal((B, L)).astype(np.float32)
+
+
+def repair_bounds(w, c, marked, T):
+    """What the fp32 log-domain pass resolves of marked blocks: its local fields,
+    k2 (w - c)^2 log2 units, round twice by 2^-24 of themselves, which changes
+    probabilities by that times ln 2, and w_soft by that times the distance
+    between the clusters; a missing or doubled repair is of the order of 1."""
+    k2 = 1.4426950408889634 / (2 * T)
+    d = np.abs(w[marked]).max() + np.median(np.abs(c))
+    rel = 2.0 ** -23 * np.log(2.0) * k2 * d * d
+    return rel, rel * 2 * np.median(np.abs(c))
+
+
+@pytest.mark.parametrize("n,k", [(2, 1), (5, 1), (8, 1), (12, 1), (4, 2), (6, 2), (8, 2), (9, 2), (10, 2), (12, 2),
+                                 (14, 2), (15, 2), (6, 3), (9, 3), (10, 3), (13, 3)])
+def test_marked_blocks_are_recomputed(n, k):
+    """Marked blocks among others (of the same wave and workgroup too): every
+    output of the repair pass, and dCodebook as the sum of both passes', against
+    the oracle; and in ever smaller workspaces, whose slots both passes use
+    again, the same bits (dCodebook is summed in another order in fp64) until
+    the log-domain kernels take over."""
+    T, marked, B = 0.25, [0, 3, 4, 8], 9
+    w, c, g = clusters(n, k, B, 20, marked)
+    ref = O.soft_codeword_vjp(w, c, n, k, T, g)
+    rest = [b for b in range(B) if b not in marked]
+    rel, tol = repair_bounds(w, c, marked, T)
+    full = P.bcjr_workspace_bytes(B, 20, n, k, P.OP_FWD_VJP)
+    for dc in (False, True):
+        out, flags = call(w, c, g, n, k, T, dc)
+        assert flags[marked].all() and set(flags) <= {0, 1} and not flags.all()
+        assert np.abs(out[0][rest] - ref[0][rest]).max() <= 2e-5
+        assert np.abs(out[0] - ref[0]).max() <= 2e-5 + tol
+        assert np.abs(out[1] / ref[1] - 1).max() <= 1e-4
+        # (means over pairs of probabilities: twice the relative change, and
+        # dCodebook's over the distance of up to 2 x 7.5 / T beside g)
+        assert grad_err(out[2], ref[2]) <= 1e-4 + 2 * rel
+        if dc:
+            assert grad_err(out[3], ref[3]) <= 1e-4 + 30 * rel
+        ran = 0
+        for part in (0.75, 0.5, 0.35, 0.25, 0.15):
+            try:
+                less, fl = call(w, c, g, n, k, T, dc, int(full * part))
+            except P.BcjrError as e:
+                assert e.status == -3
+                continue
+            if not set(fl) <= {0, 1}:
+                continue
+            ran += 1
+            assert np.array_equal(fl, flags)
+            for a, b in zip(less[:3], out[:3]):
+                np.testing.assert_array_equal(a, b)
+            if dc:
+                np.testing.assert_allclose(less[3], out[3], rtol=2.0 ** -22, atol=2.0 ** -22 * np.abs(out[3]).max())
+        print(f"[lin-small] repair n={n} k={k} dc={dc}: {ran} smaller workspaces", file=sys.__stderr__, flush=True)
+    soft = P.bcjr_soft_codeword(dev(w), dev(c), n, k, T)
+    assert np.abs(soft[0].cpu().numpy() - ref[0]).max() <= 2e-5 + tol
+    assert np.abs(soft[1].cpu().numpy() / ref[1] - 1).max() <= 1e-4
