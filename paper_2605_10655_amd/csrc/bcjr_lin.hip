@@ -20,15 +20,22 @@ LinShape group_shape(bool vjp, bool dc) {
 }
 
 template <int KB, int n, int SGT>
-LinShape sg_shape(bool vjp, bool dc) {
+LinShape sg_form(const void* fn, bool vjp) {
   constexpr int tpb = (1 << (n - 2 * KB)) / SGT;
   LinShape s;
-  s.fn = !vjp ? (const void*)lin_sg_kernel<KB, n, SGT, false, false>
-         : dc ? (const void*)lin_sg_kernel<KB, n, SGT, true, true> : (const void*)lin_sg_kernel<KB, n, SGT, true, false>;
+  s.fn = fn;
   s.nt = lin::sg_threads(n, KB, SGT);
   s.bpw = tpb > 64 ? 1 : 64 / tpb;
   s.lds = lin::sg_lds(n, KB, SGT, vjp);
   return s;
+}
+
+// SGT super-groups per lane, with dCodebook SDC
+template <int KB, int n, int SGT, int SDC = SGT>
+LinShape sg_shape(bool vjp, bool dc) {
+  if (!vjp) return sg_form<KB, n, SGT>((const void*)lin_sg_kernel<KB, n, SGT, false, false>, false);
+  if (!dc) return sg_form<KB, n, SGT>((const void*)lin_sg_kernel<KB, n, SGT, true, false>, true);
+  return sg_form<KB, n, SDC>((const void*)lin_sg_kernel<KB, n, SDC, true, true>, true);
 }
 
 }  // namespace
@@ -62,7 +69,7 @@ LinShape lin_shape(int n, int k, bool vjp, bool dc) {
     case 32 + 11: return sg_shape<2, 11, 1>(vjp, dc);
     case 32 + 12: return sg_shape<2, 12, 1>(vjp, dc);
     case 32 + 13: return sg_shape<2, 13, 1>(vjp, dc);
-    case 32 + 14: return dc ? sg_shape<2, 14, 1>(vjp, dc) : sg_shape<2, 14, 2>(vjp, dc);
+    case 32 + 14: return sg_shape<2, 14, 2, 1>(vjp, dc);
     case 32 + 15: return sg_shape<2, 15, 4>(vjp, dc);
     case 48 + 6: return group_shape<3, 6>(vjp, dc);
     case 48 + 7: return group_shape<3, 7>(vjp, dc);

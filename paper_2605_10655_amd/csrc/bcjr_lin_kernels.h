@@ -72,9 +72,11 @@ constexpr int sg_threads(int n, int KB, int SGT) {
   return tpb > 64 ? tpb : 64;
 }
 
-// waves per SIMD the register budget is cut for: 16 states per lane fit 128
-// registers with their sums, 64 states 256; at n = 15 the LDS holds one
-// workgroup of two waves per SIMD anyway
+// waves per SIMD the register budget is cut for: 128 registers for 16 states per
+// lane, 256 for 64; at n = 15 the LDS holds one workgroup of two waves per SIMD
+// anyway.  With dCodebook's sums the budget does not hold all values everywhere:
+// the compiler spills 32 and 35 registers at n = 14 and 9 of k = 2, 15 and 21 at
+// n = 8 and 9 of k = 1, and 35 to 88 at k = 3; without dCodebook 0 to 11.
 constexpr int min_waves(int KB, int SGT, bool VJP) {
   const int states = SGT << (2 * KB);
   return states <= 32 && SGT <= 4 ? (VJP ? 4 : 5) : VJP ? 2 : 3;
@@ -579,7 +581,8 @@ __global__ void __launch_bounds__(64, KB == 3 ? 3 : 4) lin_group_kernel(LinArgs 
         lin::sum_batch<GS, Q, NM>(mom, ln, r);
         const int t = t0 + (lv / (GS / Q));
         const float wt = __shfl(rw.cw - rw.cm, (ln & ~(GS - 1)) + t - rw.base);
-        if (t < L && valid && lv % (GS / Q) == 0) lin::step_outputs<VJP>(a, bb * L + t, wt, rw.ge(), r, bad);
+        if (t < L && valid && lv % (GS / Q) == 0)
+          lin::step_outputs<VJP>(a, bb * L + t, wt, rw.ge(), r, bad);
         lin::wave_sync();
       }
     }
@@ -1043,7 +1046,8 @@ __global__ void __launch_bounds__(lin::sg_threads(n, KB, SGT), lin::min_waves(KB
         } else {
           const int ts = t0 + (ln & (W - 1)) / (W / Q);
           const float ws = __shfl(rw.cw - rw.cm, (ln & ~(W - 1)) + ts - rw.base);
-          if (ts < L && valid && (ln & (W - 1)) % (W / Q) == 0) lin::step_outputs<VJP>(a, bb * L + ts, ws, rw.ge(), r, bad);
+          if (ts < L && valid && (ln & (W - 1)) % (W / Q) == 0)
+            lin::step_outputs<VJP>(a, bb * L + ts, ws, rw.ge(), r, bad);
         }
       }
       ex -= off;

@@ -188,10 +188,6 @@ __device__ __forceinline__ void lse_merge(double& m, double& s, double& y, doubl
   }
 }
 
-// The entries and LDS tables of a block are written and read by its one
-// wave only, whose memory operations take effect in program order: a fence
-// at wavefront scope keeps the compiler from reordering them and emits no
-// wait.
 // A value that is uniform, held in a vector register all the same: the
 // min-sum sweeps are bound by VALU issue, and an fp32 add or multiply with a
 // scalar operand issues at half rate (1.05 against 1.75 ns per wave and SIMD).
@@ -199,6 +195,10 @@ __device__ __forceinline__ void lse_merge(double& m, double& s, double& y, doubl
 // sum-product 2048 blocks at T = 0.0072 with dCodebook went from 20.4 to 15.0 ms.
 __device__ __forceinline__ void to_vgpr(float& x) { asm volatile("" : "+v"(x)); }
 
+// The entries and LDS tables of a block are written and read by its one
+// wave only, whose memory operations take effect in program order: a fence
+// at wavefront scope keeps the compiler from reordering them and emits no
+// wait.
 __device__ __forceinline__ void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); }
 
 // state of bit `bit` of word `q`

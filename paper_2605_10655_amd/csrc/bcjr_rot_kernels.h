@@ -445,8 +445,8 @@ __device__ __forceinline__ int exp_of(float x) { return (int)((__float_as_uint(x
 // are products of the two sweeps' values, scale-invariant per step.
 //
 // A block whose vectors leave that range -- a step whose largest entry
-// falls below 2^-30 (a single-step decay of 80 log2 units, which the
-// posterior states would not survive), the forward's per-step mass
+// falls below 2^-30 (with dCodebook 2^-36: a single-step decay of 80 or 126 log2
+// units, which the posterior states would not survive), the forward's per-step mass
 // sum_s alpha_t beta_t departing from Z by more than 2e-4 log2 units, alpha H
 // of a step so small that a better path may have been lost (kMassMin), or a
 // step's tangent moments not finite -- is marked in a.flags and recomputed by
@@ -458,6 +458,8 @@ __device__ __forceinline__ int exp_of(float x) { return (int)((__float_as_uint(x
 // ahead.  2048 blocks of 256 at T = 0.1: 57.8 ms in fb_kernel, which stores
 // (G, A) for a third sweep (40 bytes of history per group-step, here 16),
 // 35.0 ms here; bound by the step's dependency chain at two waves per SIMD.
+// The compiler spills 47 of its registers (7 in the soft-codeword form, none
+// with dW alone).
 template <int NT, bool VJP, bool DC>
 __global__ void __launch_bounds__(NT) fb_kernel_lin(FbArgs a) {
   constexpr int KB = 2, K = 4, n = 16;

@@ -7,7 +7,9 @@ the codebook's range) among ordinary ones.  Everything is compared with the
 fp64 oracle.
 
 Tolerances as everywhere: w_soft |err| <= 2e-5, logZ 1e-4 relative (of 1 where
-logZ is smaller: it crosses zero at short blocks), gradients 1e-4 of max(|ref_i|, rms(ref)) over the call's whole output.
+logZ is smaller: it crosses zero at short blocks), gradients 1e-4 of
+max(|ref_i|, rms(ref)) over the call's whole output; where the blocks are built
+to leave the number range, with the bound that the repair pass's fp32 sets.
 """
 import sys
 
@@ -44,9 +46,6 @@ def grad_err(gpu, ref):
 
 
 def check(w, c, g, n, k, T, dc, tag, rows=slice(None)):
-    """A term of dCodebook is (w - c)(X - E X) / T, where X sums g (c - w): with
-    a weight at distance D outside the codebook, X carries rounding of 2^-22
-    max|g D| (two roundings of each sweep), and the term D / T times that."""
     ws, lz, dW, dC = P.bcjr_soft_codeword_fwd_vjp(dev(w), dev(c), n, k, T, dev(g), want_dCodebook=dc)
     soft, lz0 = P.bcjr_soft_codeword(dev(w), dev(c), n, k, T)
     ows, olz, odW, odC = O.soft_codeword_vjp(w, c, n, k, T, g)
@@ -55,15 +54,12 @@ def check(w, c, g, n, k, T, dc, tag, rows=slice(None)):
     den = np.maximum(np.abs(olz), 1.0)
     e = [float(np.abs(ws - ows).max()), float(np.abs(soft - ows).max()), float((np.abs(lz - olz) / den).max()),
          float((np.abs(lz0 - olz) / den).max()), grad_err(dW, odW)]
-    slack = 0.0
     if dc:
         e.append(grad_err(dC.cpu().numpy(), odC))
-        D = np.maximum(0.0, np.maximum(w - c.max(), c.min() - w))[rows]
-        slack = float(D.max() / T * 2.0 ** -22 * np.abs(g[rows] * D).max() / np.sqrt(np.mean(odC * odC)))
     print(f"[lin-small] {tag} errors {['%.1e' % x for x in e]}", file=sys.__stderr__, flush=True)
     assert e[0] <= 2e-5 and e[1] <= 2e-5
     assert max(e[2:5]) <= 1e-4
-    assert not dc or e[5] <= 1e-4 + slack
+    assert not dc or e[5] <= 1e-4
 
 
 @pytest.mark.parametrize("n,k", SHAPES)

@@ -2,8 +2,8 @@
 65536, k = 2, fused w_soft + logZ + dW, T >= 0.04) against the fp64 oracle,
 on lengths around the layout's period of 7 steps, L = 1, several
 temperatures, the persistent loop and every grid size of a small batch; and
-of the dCodebook call at the same shape (which keeps fb_kernel's
-two-barrier exchange) on the same cases, against the oracle and against the
+of the dCodebook call at the same shape (the linear-domain kernel's form with
+the sums in its forward sweep) on the same cases, against the oracle and against the
 rotating kernel.
 
 Tolerances as everywhere: w_soft |err| <= 2e-5, logZ 1e-4 relative, dW 1e-4

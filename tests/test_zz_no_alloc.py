@@ -80,11 +80,11 @@ def _compare(got, ref, what):
 
 
 def test_noalloc_matches_workspace_entry_point_on_two_calls(lib):
-    # first call: the S = 65536 fp32 kernel with dCodebook; the scratch holds
-    # 20 of its 12.5 MiB block slots, so four workgroups run a second block
+    # first call: the S = 65536 linear-domain kernel with dCodebook; the scratch
+    # holds 39 of its 6.5 MiB block slots, so nine workgroups run a second block
     # (the workspace call runs one block per workgroup)
-    w, c, g = WL.random_case(9001, 24, 48, 16)
-    _say("[noalloc] call 1: n=16 k=2 B=24 L=48 T=0.05")
+    w, c, g = WL.random_case(9001, 48, 48, 16)
+    _say("[noalloc] call 1: n=16 k=2 B=48 L=48 T=0.05")
     _compare(_noalloc(lib, w, c, 16, 2, 0.05, g), _reference(w, c, 16, 2, 0.05, g), "call 1")
     # second, smaller call on the same scratch: another trellis and the
     # double-float kernel, whose reference decode also lives in the scratch
