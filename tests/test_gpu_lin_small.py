@@ -67,7 +67,8 @@ def test_shapes_and_lengths_match_oracle(n, k):
     r = np.random.default_rng(100 * n + k)
     c = r.standard_normal(1 << n).astype(np.float32)
     for L, B, T, dc in ((1, 3, 0.1, True), (2, 5, 0.3, True), (7, 37, 0.05, False),
-                        (66, 3, 0.1, True), (129, 5 if n < 12 else 2, 0.05, True)):
+                        (66, 3, 0.1, True), (129, 5 if n < 12 else 2, 0.05, True), (130, 3, 0.25, False)):
+        # (at k = 1 the linear-domain kernels serve from T = 0.1 on, some forms from 0.2)
         w = r.standard_normal((B, L)).astype(np.float32)
         g = r.standard_normal((B, L)).astype(np.float32)
         check(w, c, g, n, k, T, dc, f"n={n} k={k} L={L} B={B} T={T} dc={dc}")
