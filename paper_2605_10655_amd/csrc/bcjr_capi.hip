@@ -697,16 +697,19 @@ int reduce_dc(const double* part, int64_t slots, int64_t S, float* out, hipStrea
 // marked (2000 blocks of 200, us, log domain -> here):
 //  * k = 1, whose two predecessors leave the weights far from the codewords: at
 //    T = 0.05 4 to 24 % of the blocks are marked (S = 256, soft 405 -> 752, S = 2048
-//    with dW 1629 -> 2586), at T = 0.1 less than one in a thousand (S = 32 287 -> 107).
-//    Above 64 groups without dCodebook the gain is 0 to 17 % even unmarked, and at
-//    T = 0.1 heavy tails cost 75 %: from T = 0.2.  (With it, S = 256, T = 0.07: 749
-//    -> 1052; T = 0.1: 466.)
+//    with dW 1629 -> 2586).  Where half of the calls of 1500 blocks of 150 are free of
+//    marks the means meet.  Up to 64 groups from T = 0.065 (S = 128, soft, 274 -> 100
+//    free, 473 marked; S = 8 with dCodebook 590 -> 118).  Above, with dCodebook, up to
+//    256 groups from T = 0.075 (S = 512 740 -> 346), beyond, where the repair is the
+//    smaller part, from T = 0.06 (S = 2048 3512 -> 2325, heavy tails 3328; T = 0.05: 3275
+//    and 3919); without it the gain is less, from T = 0.085 (S = 512 398 -> 274, S = 4096
+//    1137 -> 899, S = 16384 3748 -> 3521; marked, S = 2048, 1168 -> 1275).
 //  * the soft codeword at T < 0.04: S = 128 at T = 0.0225 407 -> 945, S = 512 444 ->
 //    640; from 4096 states no slower at T = 0.0225 (1384 -> 1350; S = 16384, 800
 //    blocks 1985 -> 1653, but 2004 -> 2415 at T = 0.021).
 bool lin_small_ok(int n, int k, float T, bool vjp, bool dc) {
   if (!supported(n, k) || (n == 16 && k == 2)) return false;
-  if (k == 1) return T >= (dc || n < 8 ? 0.1f : 0.2f);
+  if (k == 1) return T >= (n < 8 ? 0.065f : !dc ? 0.085f : n < 10 ? 0.075f : 0.06f);
   if (vjp || n < 12) return !use_high_precision(T);
   return T >= 0.0225f;
 }

@@ -68,7 +68,7 @@ def test_shapes_and_lengths_match_oracle(n, k):
     c = r.standard_normal(1 << n).astype(np.float32)
     for L, B, T, dc in ((1, 3, 0.1, True), (2, 5, 0.3, True), (7, 37, 0.05, False),
                         (66, 3, 0.1, True), (129, 5 if n < 12 else 2, 0.05, True), (130, 3, 0.25, False)):
-        # (at k = 1 the linear-domain kernels serve from T = 0.1 on, some forms from 0.2)
+        # (at k = 1 the linear-domain kernels serve from T = 0.06 to 0.1 on, by form)
         w = r.standard_normal((B, L)).astype(np.float32)
         g = r.standard_normal((B, L)).astype(np.float32)
         check(w, c, g, n, k, T, dc, f"n={n} k={k} L={L} B={B} T={T} dc={dc}")
@@ -225,7 +225,8 @@ def test_a_path_that_both_sweeps_lose_marks_its_block(n, k):
 
 
 @pytest.mark.parametrize("n,k,T,served", [
-    (5, 1, 0.09, ""), (5, 1, 0.11, "soft dw dc"), (8, 1, 0.11, "dc"), (8, 1, 0.21, "soft dw dc"),
+    (5, 1, 0.064, ""), (5, 1, 0.066, "soft dw dc"), (9, 1, 0.074, ""), (9, 1, 0.076, "dc"), (10, 1, 0.059, ""),
+    (10, 1, 0.084, "dc"), (8, 1, 0.086, "soft dw dc"),
     (6, 2, 0.039, ""), (6, 2, 0.041, "soft dw dc"), (12, 2, 0.022, ""), (12, 2, 0.023, "soft"),
     (11, 3, 0.039, ""), (12, 3, 0.023, "soft")])
 def test_temperatures_that_the_linear_kernels_serve(n, k, T, served):
